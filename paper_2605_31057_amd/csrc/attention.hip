@@ -113,17 +113,26 @@ __device__ __forceinline__ float pair_max(float x) {
 constexpr int SLAB_ROW = 64;
 __device__ __forceinline__ int xsw(int row) { return (row >> 2) & 3; }
 
-template <int BLOCK>
 struct Tile {
-  static constexpr int NW = 2 * BLOCK / 32;         // waves (32 query rows each)
+  static constexpr int NW = 8;                      // waves
   static constexpr int NT = NW * 64;                // threads
-  static constexpr int KTW = BLOCK / 32;            // 32-key tiles per step
-  static constexpr int SLAB = BLOCK * SLAB_ROW;     // bytes per slab
-  static constexpr int BYTES = 4 * SLAB;            // bytes per tile
-  static constexpr int INSTR = BYTES / 1024;        // 1 KiB wave loads per tile
-  static constexpr int LOADS = INSTR / NW;          // per wave per tile
-  static constexpr int IPS = SLAB / 1024;           // wave loads per slab
-  static_assert(LOADS * NW == INSTR, "tile load mapping");
+  static constexpr int KEYS = 128;                  // keys per step
+  static constexpr int SLAB = KEYS * SLAB_ROW;      // bytes per slab
+  static constexpr int BYTES = 4 * SLAB;            // bytes per K or V tile
+  static constexpr int LOADS = BYTES / 1024 / NW;   // 1 KiB wave loads per wave and tile
+};
+
+// How the eight waves share a tile: KG key groups of 8 / KG waves.  A wave
+// holds 32 query rows of the tile's ROWS and takes NK of the step's 128 keys
+// (key group kg: keys kg*NK .. kg*NK + NK - 1).  With KG > 1 several waves
+// hold the same rows, each over its own share of the keys, and their partial
+// results are combined at the end of the tile (combine_groups).
+template <int KG>
+struct Split {
+  static constexpr int ROWS = 256 / KG;             // query rows per tile
+  static constexpr int NRG = 8 / KG;                // waves per key group
+  static constexpr int NK = Tile::KEYS / KG;        // keys per wave and step
+  static constexpr int KTW = NK / 32;               // 32-key tiles per wave and step
 };
 
 // One wave load (1 KiB) of a K or V tile into LDS at byte address lds_dst:
@@ -160,57 +169,49 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const __bf16* head_b
 }
 
 // Per-wave load plan: wave w's load j of a tile fills tile bytes
-// 1024*(w + NW*j): slab j, rows 16*w + lane/4 (NW = IPS: one wave per 16-row
-// band of a slab), physical chunk lane%4, which holds logical chunk
-// (lane%4) ^ x(row) = (lane%4) ^ (lane/16).  Global offset: lane_off plus
-// 64*j; LDS offset: lds_w plus 1024*NW*j.
-template <int BLOCK>
+// 1024*(w + NW*j): slab j, rows 16*w + lane/4, physical chunk lane%4, which
+// holds logical chunk (lane%4) ^ x(row) = (lane%4) ^ (lane/16).  Global
+// offset: lane_off plus 64*j; LDS offset: lds_w plus 1024*NW*j.  With BLOCK =
+// 64 a step's tile is two key blocks, rows 0..63 and 64..127, and the
+// resource that waves 4..7 load through starts at the second one.
 struct LoadPlan {
-  uint32_t lane_off;   // (16*w + lane/4)*row_bytes + 16*((lane%4) ^ (lane/16))
+  uint32_t lane_off;   // (16*(w % (BLOCK/16)) + lane/4)*row_bytes + 16*((lane%4) ^ (lane/16))
   uint32_t lds_w;      // 1024*w (uniform)
 };
 
 template <int BLOCK>
-__device__ __forceinline__ LoadPlan<BLOCK> load_plan(uint32_t row_bytes, int wave,
-                                                     int lane) {
-  using TL = Tile<BLOCK>;
-  static_assert(TL::NW == TL::IPS, "one wave per 16-row band of a slab");
-  LoadPlan<BLOCK> lp;
-  lp.lane_off = (uint32_t)(16 * wave + lane / 4) * row_bytes +
+__device__ __forceinline__ LoadPlan load_plan(uint32_t row_bytes, int wave, int lane) {
+  LoadPlan lp;
+  lp.lane_off = (uint32_t)(16 * (wave % (BLOCK / 16)) + lane / 4) * row_bytes +
                 16u * (uint32_t)((lane % 4) ^ (lane / 16));
   lp.lds_w = (uint32_t)__builtin_amdgcn_readfirstlane(1024u * (uint32_t)wave);
   return lp;
 }
 
-template <int BLOCK>
 __device__ __forceinline__ void issue_tile(uint32_t lds, __amdgpu_buffer_rsrc_t rsrc,
-                                           const LoadPlan<BLOCK>& lp) {
-  using TL = Tile<BLOCK>;
+                                           const LoadPlan& lp) {
 #pragma unroll
-  for (int j = 0; j < TL::LOADS; ++j)
-    issue_load(lds + lp.lds_w + 1024u * TL::NW * j, rsrc, lp.lane_off + 64u * j);
+  for (int j = 0; j < Tile::LOADS; ++j)
+    issue_load(lds + lp.lds_w + 1024u * Tile::NW * j, rsrc, lp.lane_off + 64u * j);
 }
 
 // The loads of one pipeline step: the next K tile and the next V tile, spread
 // over the first phase of the step so the wave never stalls on issuing them.
 // Issued unconditionally: near the end of a row the key-block indices repeat
 // the last block and the loads land in slots no later step reads.
-template <int BLOCK>
 struct StepLoads {
   uint32_t k_dst, v_dst;                 // LDS tile addresses
   __amdgpu_buffer_rsrc_t rk, rv;         // resources starting at the tiles
-  const LoadPlan<BLOCK>* kp;
-  const LoadPlan<BLOCK>* vp;
+  const LoadPlan* kp;
+  const LoadPlan* vp;
 };
 
-template <int BLOCK>
-__device__ __forceinline__ void issue_step_load(const StepLoads<BLOCK>& sl, int i) {
-  using TL = Tile<BLOCK>;
-  if (i < TL::LOADS)
-    issue_load(sl.k_dst + sl.kp->lds_w + 1024u * TL::NW * i, sl.rk, sl.kp->lane_off + 64u * i);
+__device__ __forceinline__ void issue_step_load(const StepLoads& sl, int i) {
+  if (i < Tile::LOADS)
+    issue_load(sl.k_dst + sl.kp->lds_w + 1024u * Tile::NW * i, sl.rk, sl.kp->lane_off + 64u * i);
   else
-    issue_load(sl.v_dst + sl.vp->lds_w + 1024u * TL::NW * (i - TL::LOADS), sl.rv,
-               sl.vp->lane_off + 64u * (i - TL::LOADS));
+    issue_load(sl.v_dst + sl.vp->lds_w + 1024u * Tile::NW * (i - Tile::LOADS), sl.rv,
+               sl.vp->lane_off + 64u * (i - Tile::LOADS));
 }
 
 __device__ __forceinline__ void wait_loads_and_sync() {
@@ -218,9 +219,9 @@ __device__ __forceinline__ void wait_loads_and_sync() {
   __syncthreads();
 }
 
-template <int BLOCK>
+template <int KTW>
 struct Scores {
-  f32x16 s[Tile<BLOCK>::KTW];   // one 32-key tile each
+  f32x16 s[KTW];   // one 32-key tile each
 };
 
 // Per-lane LDS byte offsets (within a tile) of the K and V fragments.
@@ -229,13 +230,14 @@ struct FragAddr {
   uint32_t v_lo, v_hi;      // V rows for k-slots 0..3 / 4..7 (transposing read)
 };
 
-__device__ __forceinline__ FragAddr frag_addr(int lane) {
+// `key0`: the first key of the wave's share of the step.
+__device__ __forceinline__ FragAddr frag_addr(int lane, int key0) {
   const int hl = lane / 32, li = lane % 32;
   FragAddr f;
   // K: row 32*kt + li, d = 16*stp + 8*hl: slab stp/2, logical chunk
   // 2*(stp%2) + hl.  x(row) = (li/4)%4 for every kt.
-  const int krow = li;
-  const int kx = xsw(krow);
+  const int krow = key0 + li;
+  const int kx = xsw(li);
   f.k_even = krow * SLAB_ROW + ((hl ^ kx) * 16);
   f.k_odd = krow * SLAB_ROW + (((2 + hl) ^ kx) * 16);
   // V: the transposing read gives lane (group g = lane/16, j = lane%16)
@@ -247,23 +249,22 @@ __device__ __forceinline__ FragAddr frag_addr(int lane) {
   const int vrow = 4 * (g / 2) + sl / 4;
   const int lc = 2 * (g % 2) + (sl % 4) / 2;
   const int half = (sl % 2) * 8;
-  f.v_lo = vrow * SLAB_ROW + ((lc ^ xsw(vrow)) * 16) + half;
-  f.v_hi = (vrow + 8) * SLAB_ROW + ((lc ^ xsw(vrow + 8)) * 16) + half;
+  f.v_lo = (key0 + vrow) * SLAB_ROW + ((lc ^ xsw(vrow)) * 16) + half;
+  f.v_hi = (key0 + vrow + 8) * SLAB_ROW + ((lc ^ xsw(vrow + 8)) * 16) + half;
   return f;
 }
 
-// S^T = K Q^T for the keys of one step (K tile at lds_k).
-template <int BLOCK>
+// S^T = K Q^T for the wave's keys of one step (K tile at lds_k).
+template <int KTW>
 __device__ __forceinline__ void compute_scores(const char* lds_k, const bf16x8 (&qf)[8],
-                                               Scores<BLOCK>& sc, const FragAddr& fa) {
-  using TL = Tile<BLOCK>;
+                                               Scores<KTW>& sc, const FragAddr& fa) {
 #pragma unroll
-  for (int kt = 0; kt < TL::KTW; ++kt) {
+  for (int kt = 0; kt < KTW; ++kt) {
     f32x16 acc = f32x16{};
 #pragma unroll
     for (int stp = 0; stp < 8; ++stp) {
       const uint32_t off = ((stp & 1) ? fa.k_odd : fa.k_even) +
-                           (stp / 2) * TL::SLAB + kt * 32 * SLAB_ROW;
+                           (stp / 2) * Tile::SLAB + kt * 32 * SLAB_ROW;
       const bf16x8 a = *(const bf16x8*)(lds_k + off);
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[stp], acc, 0, 0, 0);
     }
@@ -290,17 +291,16 @@ struct WaveState {
 };
 
 // Keys at or past N (ragged last block) do not exist: their scores become
-// -inf.  `valid` = N - first key of the block (0: no key is valid).  Per
+// -inf.  `valid` = N - the wave's first key (at most 0: no key is valid).  Per
 // score one compare of a constant into VCC and one select, a scheduling
 // barrier every 4 scores so that few compare results are live at once.
-template <int BLOCK>
-__device__ __forceinline__ void mask_tail(Scores<BLOCK>& sc, int lane, int valid) {
-  using TL = Tile<BLOCK>;
+template <int KTW>
+__device__ __forceinline__ void mask_tail(Scores<KTW>& sc, int lane, int valid) {
   const int hl = lane / 32;
-  if (valid < BLOCK) {
+  if (valid < 32 * KTW) {
     const int lim = valid - 4 * hl;   // key 4*hl + c is valid iff c < lim
 #pragma unroll
-    for (int kt = 0; kt < TL::KTW; ++kt)
+    for (int kt = 0; kt < KTW; ++kt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);
@@ -326,21 +326,21 @@ __device__ __forceinline__ void mask_tail(Scores<BLOCK>& sc, int lane, int valid
 //
 // The lane's query row lies in the second frame iff its row index within the
 // wave's 32 rows reaches `sec_from` (wave-uniform); the lane index is
-// recomputed here rather than held in a register through the loop.
-template <int BLOCK>
-__device__ __forceinline__ void mask_exact(Scores<BLOCK>& sc, uint32_t pat, int kfirst,
-                                           int valid, int sec_from) {
-  using TL = Tile<BLOCK>;
+// recomputed here rather than held in a register through the loop.  `koff`
+// is the wave's first key within the key block.
+template <int BLOCK, int KTW>
+__device__ __forceinline__ void mask_exact(Scores<KTW>& sc, uint32_t pat, int kfirst,
+                                           int valid, int sec_from, int koff) {
   if (pat != 0xFu || valid < BLOCK) {
     const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     const int hl = lane / 32, li = lane % 32;
     const uint32_t bits = li >= sec_from ? pat >> 2 : pat;
     const int klo = (bits & 1u) ? 0 : kfirst;
     const int khi = (bits & 2u) ? valid : min(kfirst, valid);
-    const uint32_t shift = (uint32_t)(4 * hl - klo);
+    const uint32_t shift = (uint32_t)(koff + 4 * hl - klo);
     const uint32_t width = (uint32_t)max(khi - klo, 0);
 #pragma unroll
-    for (int kt = 0; kt < TL::KTW; ++kt)
+    for (int kt = 0; kt < KTW; ++kt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);
@@ -350,9 +350,9 @@ __device__ __forceinline__ void mask_exact(Scores<BLOCK>& sc, uint32_t pat, int 
   }
 }
 
-template <int BLOCK>
+template <int KTW>
 struct Probs {
-  bf16x8 p[Tile<BLOCK>::KTW][2];   // [key tile][k-step half]
+  bf16x8 p[KTW][2];   // [key tile][k-step half]
 };
 
 // Softmax phase of the ping-pong schedule: block j's scores (in `sc`) become
@@ -363,13 +363,12 @@ struct Probs {
 // loads to issue along the way.  Scheduling barriers every 8 scores keep the
 // compiler from hoisting many exponentials at once (S, P, O and Q already
 // fill the register file).
-template <int BLOCK, int RSUM>
-__device__ __forceinline__ void softmax_phase(const Scores<BLOCK>& sc, WaveState& st,
-                                              Probs<BLOCK>& pr, float scale_log2,
-                                              const StepLoads<BLOCK>* sl) {
-  using TL = Tile<BLOCK>;
-  constexpr int NE = 16 * TL::KTW;   // scores per lane
-  constexpr int NLOADS = 2 * TL::LOADS;
+template <int KTW, int RSUM>
+__device__ __forceinline__ void softmax_phase(const Scores<KTW>& sc, WaveState& st,
+                                              Probs<KTW>& pr, float scale_log2,
+                                              const StepLoads* sl) {
+  constexpr int NE = 16 * KTW;   // scores per lane
+  constexpr int NLOADS = 2 * Tile::LOADS;
   constexpr int LOAD_EVERY = NE / NLOADS >= 2 ? NE / NLOADS : 2;   // scores per load
   int issued = 0;
   float mx = -__builtin_inff();
@@ -396,7 +395,7 @@ __device__ __forceinline__ void softmax_phase(const Scores<BLOCK>& sc, WaveState
 #pragma unroll
   for (int el = 0; el < NE; el += 2) {
     if (el % 8 == 0) __builtin_amdgcn_sched_barrier(0);
-    if (sl && el % LOAD_EVERY == 0 && issued < NLOADS) issue_step_load<BLOCK>(*sl, issued++);
+    if (sl && el % LOAD_EVERY == 0 && issued < NLOADS) issue_step_load(*sl, issued++);
     const float a =
         __builtin_amdgcn_exp2f(__builtin_fmaf(sc.s[el / 16][el % 16], scale_log2, -msub));
     const float b = __builtin_amdgcn_exp2f(
@@ -409,7 +408,7 @@ __device__ __forceinline__ void softmax_phase(const Scores<BLOCK>& sc, WaveState
     pr.p[el / 16][(el % 16) / 8][el % 8 + 1] = pk[1];
   }
   if (sl)
-    for (; issued < NLOADS; ++issued) issue_step_load<BLOCK>(*sl, issued);
+    for (; issued < NLOADS; ++issued) issue_step_load(*sl, issued);
 }
 
 // GEMM phase of the ping-pong schedule: with RSUM_MFMA, l += the row sums of
@@ -419,18 +418,17 @@ __device__ __forceinline__ void softmax_phase(const Scores<BLOCK>& sc, WaveState
 // the phase.  The row-sum MFMAs come first: their operands are already in
 // registers, so they run while the first fragments arrive from LDS (0.2-1.2%
 // faster than after P V, interleaved on one board).
-template <int BLOCK, int RSUM>
+template <int KTW, int RSUM>
 __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
-                                           const bf16x8 (&qf)[8], Scores<BLOCK>& sc,
-                                           const Probs<BLOCK>& pr, WaveState& st,
+                                           const bf16x8 (&qf)[8], Scores<KTW>& sc,
+                                           const Probs<KTW>& pr, WaveState& st,
                                            const FragAddr& fa, const bf16x8& ones,
-                                           const StepLoads<BLOCK>* sl) {
-  using TL = Tile<BLOCK>;
-  constexpr int NS = 8 * TL::KTW;   // S MFMAs: (key tile, d-step)
-  constexpr int NP = 8 * TL::KTW;   // PV fragments: (d tile, key tile, k-step half)
+                                           const StepLoads* sl) {
+  constexpr int NS = 8 * KTW;   // S MFMAs: (key tile, d-step)
+  constexpr int NP = 8 * KTW;   // PV fragments: (d tile, key tile, k-step half)
   constexpr int NF = NS + NP;
   constexpr int AHEAD = 3;
-  constexpr int NLOADS = 2 * TL::LOADS;
+  constexpr int NLOADS = 2 * Tile::LOADS;
   // Fragment i < NP: V^T, d tile i/(2*KTW), key tile (i/2)%KTW, k-step half
   // i%2.  Fragment NP + f: K, key tile f/8, d-step f%8.  MFMAs on one
   // accumulator follow each other, and P(j) (with its row sums) is done
@@ -439,12 +437,12 @@ __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
     if (i >= NP) {
       const int f = i - NP;
       const int kt = f / 8, stp = f % 8;
-      const uint32_t off = ((stp & 1) ? fa.k_odd : fa.k_even) + (stp / 2) * TL::SLAB +
+      const uint32_t off = ((stp & 1) ? fa.k_odd : fa.k_even) + (stp / 2) * Tile::SLAB +
                            kt * 32 * SLAB_ROW;
       return *(const bf16x8*)(lds_k + off);
     }
-    const int dt = i / (2 * TL::KTW), kt = (i / 2) % TL::KTW, c = i % 2;
-    const uint32_t off = dt * TL::SLAB + (32 * kt + 16 * c) * SLAB_ROW;
+    const int dt = i / (2 * KTW), kt = (i / 2) % KTW, c = i % 2;
+    const uint32_t off = dt * Tile::SLAB + (32 * kt + 16 * c) * SLAB_ROW;
     const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(lds_v + fa.v_lo + off));
     const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(lds_v + fa.v_hi + off));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -455,7 +453,7 @@ __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (RSUM == RSUM_MFMA) {
 #pragma unroll
-    for (int kt2 = 0; kt2 < TL::KTW; ++kt2)
+    for (int kt2 = 0; kt2 < KTW; ++kt2)
 #pragma unroll
       for (int c2 = 0; c2 < 2; ++c2) {
         st.l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pr.p[kt2][c2], st.l, 0, 0, 0);
@@ -465,9 +463,9 @@ __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
 #pragma unroll
   for (int i = 0; i < NF; ++i) {
     if (i + AHEAD < NF) fr[i + AHEAD] = frag(i + AHEAD);
-    if (sl && i % (NF / NLOADS) == 0) issue_step_load<BLOCK>(*sl, i / (NF / NLOADS));
+    if (sl && i % (NF / NLOADS) == 0) issue_step_load(*sl, i / (NF / NLOADS));
     if (i < NP) {
-      const int dt = i / (2 * TL::KTW), kt = (i / 2) % TL::KTW, c = i % 2;
+      const int dt = i / (2 * KTW), kt = (i / 2) % KTW, c = i % 2;
       st.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], pr.p[kt][c], st.o[dt], 0, 0, 0);
     } else {
       const int f = i - NP;
@@ -489,7 +487,7 @@ struct WalkLds {
   uint32_t w[WALK_CAP];       // step words, in walk order
   int32_t cnt[2][16][5];      // per-wave counts of a merge pass (double-buffered)
 };
-static_assert(2 * WALK_CAP * 4 <= 4 * Tile<64>::BYTES, "rows staged in the tile buffers");
+static_assert(2 * WALK_CAP * 4 <= 4 * Tile::BYTES, "rows staged in the tile buffers");
 
 // Step words.  Block form (row entries are key blocks): kb in bits 0..29,
 // bit 30 / 31 set when row 0 / row 1 keeps kb.  Token-exact form (row
@@ -601,21 +599,104 @@ __device__ __forceinline__ int32_t merge_pair(WalkLds& L, uint32_t* stage,
   return __builtin_amdgcn_readfirstlane(min(words, WALK_CAP));
 }
 
+// The step words of a tile that lies in one query block: its CSR row, largest
+// key first.  Returns the number of words (ends with a barrier).
+template <bool EXACT>
+__device__ __forceinline__ int32_t single_row(WalkLds& L, const uint32_t* __restrict__ rows,
+                                              int32_t lo, int32_t hi, int32_t nb) {
+  const int n = max(0, min(hi - lo, WALK_CAP));
+  for (int t = threadIdx.x; t < n; t += Tile::NT)
+    L.w[t] = step_word<EXACT>(rows[hi - 1 - t], 0u, true, false, nb);
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(n);
+}
+
+// Combines the key groups' partial results (KG > 1) and stores the tile's
+// rows: each of the KG waves that hold the same rows keeps 4 / KG of the four
+// d tiles and takes the others' parts of them through LDS.  With m = max m_g,
+// O = sum_g 2^(m_g - m) O_g and l = sum_g 2^(m_g - m) l_g, added in the order
+// of the groups.  `xch`: the tile buffers, idle here; wave w's part of d tile
+// dt is the 4 KB at 4096*(4*w + dt), and the slot of a d tile the wave keeps
+// holds its rows' (m, l).
+template <int KG>
+__device__ __forceinline__ void combine_groups(char* xch, WaveState& st, float lsum,
+                                               __bf16* orow, bool row_ok, int wave, int lane) {
+  using SP = Split<KG>;
+  constexpr int KEEP = 4 / KG;
+  const int rg = wave % SP::NRG, kg = wave / SP::NRG;
+  const int li = lane % 32, hl = lane / 32;
+  auto slot = [&](int w, int dt) { return xch + 4096 * (4 * w + dt); };
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) {
+    if (dt / KEEP == kg) continue;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      *(f32x4*)(slot(wave, dt) + 1024 * a + 16 * lane) =
+          f32x4{st.o[dt][4 * a], st.o[dt][4 * a + 1], st.o[dt][4 * a + 2], st.o[dt][4 * a + 3]};
+  }
+  if (hl == 0) {
+    float* const ml = (float*)(slot(wave, kg * KEEP) + 8 * li);
+    ml[0] = st.m;
+    ml[1] = lsum;
+  }
+  __syncthreads();
+  float m = -__builtin_inff();
+#pragma unroll
+  for (int g = 0; g < KG; ++g)
+    m = fmaxf(m, *(const float*)(slot(g * SP::NRG + rg, g * KEEP) + 8 * li));
+  float f[KG], l = 0.f;
+#pragma unroll
+  for (int g = 0; g < KG; ++g) {
+    const float* const ml = (const float*)(slot(g * SP::NRG + rg, g * KEEP) + 8 * li);
+    f[g] = ml[0] == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(ml[0] - m);
+    l += ml[1] * f[g];
+  }
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) {
+    if (dt / KEEP != kg) continue;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      f32x4 acc = f32x4{};
+#pragma unroll
+      for (int g = 0; g < KG; ++g) {
+        const f32x4 part =
+            g == kg ? f32x4{st.o[dt][4 * a], st.o[dt][4 * a + 1], st.o[dt][4 * a + 2],
+                            st.o[dt][4 * a + 3]}
+                    : *(const f32x4*)(slot(g * SP::NRG + rg, dt) + 1024 * a + 16 * lane);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[b] += part[b] * f[g];
+      }
+      typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+      bf16x4 w;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) w[b] = (__bf16)(acc[b] * inv);
+      if (row_ok) *(bf16x4*)(orow + 32 * dt + 8 * a + 4 * hl) = w;
+    }
+  }
+}
+
 // MODE: ATTN_DENSE (every key block), ATTN_BLOCK (CSR rows of key blocks),
 // ATTN_EXACT (CSR rows of token-exact entry words).
-// One tile: head `tile / npairs`, pair of query blocks from `tile % npairs`,
-// using the workgroup's LDS stages `lds` (K slots 0-1, V slots 0-1).
-template <int BLOCK, int MODE>
+// One tile: rows row0 .. row0 + ROWS - 1 of head `head`, using the
+// workgroup's LDS stages `lds` (K slots 0-1, V slots 0-1).  The tile lies in
+// one query block or covers two whole ones (2p and 2p + 1).
+template <int BLOCK, int MODE, int KG>
 __device__ __forceinline__ void attn_tile(
-    char* lds, WalkLds& walk, int tile, const __bf16* __restrict__ qg, const __bf16* __restrict__ kg,
-    const __bf16* __restrict__ vg, __bf16* __restrict__ og, int64_t q_sh,
-    int64_t q_st, int64_t k_sh, int64_t k_st, int64_t v_sh, int64_t v_st,
-    int64_t o_sh, int64_t o_st, int32_t H, int32_t N, int32_t nb,
-    const int32_t* __restrict__ row_ptr, const uint32_t* __restrict__ rows,
-    int32_t P, float scale_log2) {
-  using TL = Tile<BLOCK>;
+    char* lds, WalkLds& walk, int head, int row0, const __bf16* __restrict__ qg,
+    const __bf16* __restrict__ kg_, const __bf16* __restrict__ vg, __bf16* __restrict__ og,
+    int64_t q_sh, int64_t q_st, int64_t k_sh, int64_t k_st, int64_t v_sh, int64_t v_st,
+    int64_t o_sh, int64_t o_st, int32_t N, int32_t nb, const int32_t* __restrict__ row_ptr,
+    const uint32_t* __restrict__ rows, int32_t P, float scale_log2) {
+  using TL = Tile;
+  using SP = Split<KG>;
+  constexpr int KTW = SP::KTW;
   constexpr bool SPARSE = MODE != ATTN_DENSE;
   constexpr bool EXACT = MODE == ATTN_EXACT;
+  constexpr bool PAIR = SP::ROWS > BLOCK;        // two query blocks, else (part of) one
+  constexpr int SUBS = TL::KEYS / BLOCK;         // key blocks per step
+  static_assert(SP::ROWS <= 2 * BLOCK, "a tile covers at most two query blocks");
+  static_assert(SP::NK <= BLOCK, "a wave's keys lie in one key block");
   const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void*)lds;
 
   const int tid = threadIdx.x;
@@ -624,26 +705,24 @@ __device__ __forceinline__ void attn_tile(
   const int hl = lane / 32;
   const int li = lane % 32;
 
-  const int npairs = (nb + 1) / 2;
-  const int head = tile / npairs;
-  // Pairs of a head go last to first: rows that attend every key block (text
-  // tokens, placed after the video tokens) are the longest tiles, and taking
-  // them first keeps them out of the grid's tail (each row's key blocks are
-  // then walked in descending order, which keeps neighbouring workgroups'
-  // shared blocks in L2).
-  const int pq = npairs - 1 - tile % npairs;    // query blocks 2pq, 2pq+1
-  const bool upper = wave >= TL::NW / 2;        // rows of query block 2pq+1
-  const int qb = 2 * pq + (upper ? 1 : 0);
-  const int rows0 = 32 * (wave % (TL::NW / 2));   // first row within qb
+  const int rg = wave % SP::NRG, kg = wave / SP::NRG;
+  const bool upper = wave >= TL::NW / 2;        // follows half a step behind
+  const int qb0 = row0 / BLOCK;                 // the tile's (first) query block
+  const int wrow = row0 + 32 * rg;              // the wave's first row
+  const int qb = wrow / BLOCK;
+  // The wave's first key in its key block.
+  const int koff = KG == 1 ? 0 : kg * SP::NK % BLOCK;
+  // The wave's key block of a step (and the one it loads): word SUBS*j + sub.
+  const int sub = SUBS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave / (TL::NW / 2));
 
   const __bf16* qh = qg + head * q_sh;
   __bf16* oh = og + head * o_sh;
-  const __bf16* const kh_base = kg + head * k_sh;
+  const __bf16* const kh_base = kg_ + head * k_sh;
   const __bf16* const vh_base = vg + head * v_sh;
   const uint32_t k_bytes = (uint32_t)(((int64_t)(N - 1) * k_st + D) * 2);
   const uint32_t v_bytes = (uint32_t)(((int64_t)(N - 1) * v_st + D) * 2);
-  const LoadPlan<BLOCK> kp = load_plan<BLOCK>((uint32_t)(k_st * 2), wave, lane);
-  const LoadPlan<BLOCK> vp = load_plan<BLOCK>((uint32_t)(v_st * 2), wave, lane);
+  const LoadPlan kp = load_plan<BLOCK>((uint32_t)(k_st * 2), wave, lane);
+  const LoadPlan vp = load_plan<BLOCK>((uint32_t)(v_st * 2), wave, lane);
   // Step words: key block in bits 0..29 (block form) or 0..15 (exact form).
   auto kb_of = [&](uint32_t w) {
     return (int)(EXACT ? (w & 0xFFFFu) : (w & 0x3FFFFFFFu));
@@ -654,10 +733,10 @@ __device__ __forceinline__ void attn_tile(
   auto rv_at = [&](uint32_t w) {
     return tile_rsrc<BLOCK>(vh_base, v_st, v_bytes, kb_of(w), nb);
   };
-  const FragAddr fa = frag_addr(lane);
+  const FragAddr fa = frag_addr(lane, KG == 1 ? 0 : kg * SP::NK);
 
   // Q fragments: row qrow, k-slots d = 16*stp + 8*hl + 0..7.
-  const int qrow = qb * BLOCK + rows0 + li;
+  const int qrow = wrow + li;
   bf16x8 qf[8];
 #pragma unroll
   for (int stp = 0; stp < 8; ++stp)
@@ -670,26 +749,26 @@ __device__ __forceinline__ void attn_tile(
   int sec_from = 32;
   if constexpr (EXACT) {
     const int qfirst = P - (int)(((int64_t)qb * BLOCK) % P);
-    sec_from = __builtin_amdgcn_readfirstlane(qfirst - rows0);
+    sec_from = __builtin_amdgcn_readfirstlane(qfirst - (wrow - qb * BLOCK));
   }
   // Masks the scores of the key block of step word w for this wave's query
   // block: a key block that block does not keep has no valid keys.
-  const uint32_t kept_bit = upper ? 31u : 30u;       // block form
-  const uint32_t pat_shift = upper ? 28u : 24u;      // exact form
-  auto mask_block = [&](Scores<BLOCK>& sc, uint32_t w) {
+  // `second`: the wave holds rows of query block 2p + 1.
+  auto mask_block = [&](Scores<KTW>& sc, uint32_t w, bool second) {
     const int kb = kb_of(w);
+    const uint32_t kept_bit = second ? 31u : 30u;      // block form
+    const uint32_t pat_shift = second ? 28u : 24u;     // exact form
     if constexpr (EXACT)
-      mask_exact<BLOCK>(sc, (w >> pat_shift) & 0xFu, (int)((w >> 16) & 0xFFu),
-                        N - kb * BLOCK, sec_from);
+      mask_exact<BLOCK, KTW>(sc, (w >> pat_shift) & 0xFu, (int)((w >> 16) & 0xFFu),
+                             N - kb * BLOCK, sec_from, koff);
     else
-      mask_tail<BLOCK>(sc, lane, ((w >> kept_bit) & 1u) ? N - kb * BLOCK : 0);
+      mask_tail<KTW>(sc, lane, ((w >> kept_bit) & 1u) ? N - kb * BLOCK - koff : 0);
   };
 
   // The walk (sparse modes) or the key blocks nb-1 .. 0 (dense): n steps.
   // Words of steps past the last one repeat it: their loads land in slots
   // that no later step reads.
-  int n = nb;
-  uint32_t w0 = 0u, w1 = 0u, w2 = 0u;
+  int words = nb;
   // Dense: the words nb-1 .. 0 (both query blocks keep every key block),
   // written to LDS and read from there like the merged walk's (timed faster
   // than computing them in the loop: 1.7% at the Wan-1.3B 6x shape and 2.9%
@@ -697,32 +776,45 @@ __device__ __forceinline__ void attn_tile(
   // theirs.  The block mode runs dense attention this way when it is given
   // no CSR (row_ptr null, nb <= WALK_CAP): the same code as a full mask's
   // walk, without the merge.
+  auto dense_word = [&](int i) {
+    return i < nb ? (uint32_t)(nb - 1 - i) | 0xC0000000u : 0x3FFFFFFFu;
+  };
   auto dense_words = [&]() {
     __syncthreads();
-    for (int t = threadIdx.x; t < min(nb, WALK_CAP); t += TL::NT)
-      walk.w[t] = (uint32_t)(nb - 1 - t) | 0xC0000000u;
+    for (int t = threadIdx.x; t < min(nb, WALK_CAP); t += TL::NT) walk.w[t] = dense_word(t);
     __syncthreads();
-    w0 = (uint32_t)(nb - 1) | 0xC0000000u;
-    w1 = (uint32_t)max(nb - 2, 0) | 0xC0000000u;
-    w2 = (uint32_t)max(nb - 3, 0) | 0xC0000000u;
   };
   if constexpr (SPARSE) {
     if (EXACT || row_ptr != nullptr) {
-      const int32_t r0 = __builtin_amdgcn_readfirstlane(row_ptr[2 * pq]);
-      const int32_t r1 = __builtin_amdgcn_readfirstlane(row_ptr[2 * pq + 1]);
-      const int32_t r2 =
-          2 * pq + 1 < nb ? __builtin_amdgcn_readfirstlane(row_ptr[2 * pq + 2]) : r1;
-      n = merge_pair<TL::NT, EXACT>(walk, (uint32_t*)lds, rows, r0, r1, r1, r2, nb);
-      if (n > 0) {
-        w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[0]);
-        w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[min(1, n - 1)]);
-        w2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[min(2, n - 1)]);
+      const int32_t r0 = __builtin_amdgcn_readfirstlane(row_ptr[qb0]);
+      const int32_t r1 = __builtin_amdgcn_readfirstlane(row_ptr[qb0 + 1]);
+      if constexpr (PAIR) {
+        const int32_t r2 =
+            qb0 + 1 < nb ? __builtin_amdgcn_readfirstlane(row_ptr[qb0 + 2]) : r1;
+        words = merge_pair<TL::NT, EXACT>(walk, (uint32_t*)lds, rows, r0, r1, r1, r2, nb);
+      } else {
+        words = single_row<EXACT>(walk, rows, r0, r1, nb);
       }
     } else {
       dense_words();
     }
   } else {
     dense_words();
+  }
+  if constexpr (SUBS == 2) {
+    // An odd walk ends with a word that no query block keeps and whose loads
+    // read zeros (words < WALK_CAP, which is even).
+    if (words & 1) {
+      if (tid == 0 && words < WALK_CAP) walk.w[words] = EXACT ? 0xFFFFu : 0x3FFFFFFFu;
+      __syncthreads();
+    }
+  }
+  const int n = (words + SUBS - 1) / SUBS;
+  uint32_t w0 = 0u, w1 = 0u, w2 = 0u;
+  if (n > 0) {
+    w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[sub]);
+    w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[SUBS * min(1, n - 1) + sub]);
+    w2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[SUBS * min(2, n - 1) + sub]);
   }
 
   WaveState ws;
@@ -732,7 +824,7 @@ __device__ __forceinline__ void attn_tile(
   ws.l = f32x4{};
   ws.l0 = 0.f;
   ws.l1 = 0.f;
-  constexpr int RSUM = MODE == ATTN_BLOCK ? RSUM_VALU : RSUM_MFMA;
+  constexpr int RSUM = MODE == ATTN_BLOCK || KG > 1 ? RSUM_VALU : RSUM_MFMA;
   // A operand of the row-sum MFMA (16x16x32): read as P^T's B operand, lane
   // group g = lane/16 of the 32x32 P register holds q rows 16*(g%2) + 0..15,
   // so A row 0 takes groups 0 and 2 (rows 0-15) and row 1 groups 1 and 3.
@@ -750,33 +842,37 @@ __device__ __forceinline__ void attn_tile(
     const char* const k_lds = lds;
     const char* const v_lds = lds + 2 * TL::BYTES;
 
-    // Ping-pong schedule.  The waves of query block 2pq ("leaders") run half
-    // a step ahead of those of 2pq+1, so on each SIMD one wave is in its GEMM
-    // phase (O += P(j) V(j), S(j+1) = K(j+1) Q^T: MFMA) while the other is in
-    // its softmax phase (VALU): half-period 2j is the leaders' GEMM j and the
-    // others' softmax j, half-period 2j+1 the leaders' softmax j+1 and the
-    // others' GEMM j.  A barrier ends every half-period.  K(j+1) and V(j) stay
-    // resident through half-periods 2j and 2j+1; K(j+2) and V(j+1) are issued
-    // in half-period 2j (into the slots of K(j) and V(j-1), free since
-    // half-period 2j-1) and waited for at the end of 2j+1.
-    const bool lead = !upper;
-    issue_tile<BLOCK>(k_slot0, rk_at(w0), kp);
-    issue_tile<BLOCK>(v_slot0, rv_at(w0), vp);
-    issue_tile<BLOCK>(k_slot0 + TL::BYTES, rk_at(w1), kp);
+    // Ping-pong schedule.  Waves 0..3 ("leaders") run half a step ahead of
+    // waves 4..7, so on each SIMD one wave is in its GEMM phase (O += P(j)
+    // V(j), S(j+1) = K(j+1) Q^T: MFMA) while the other is in its softmax phase
+    // (VALU): half-period 2j is the leaders' GEMM j and the others' softmax j,
+    // half-period 2j+1 the leaders' softmax j+1 and the others' GEMM j.  A
+    // barrier ends every half-period.  K(j+1) and V(j) stay resident through
+    // half-periods 2j and 2j+1; K(j+2) and V(j+1) are issued in half-period 2j
+    // (into the slots of K(j) and V(j-1), free since half-period 2j-1) and
+    // waited for at the end of 2j+1.
+    // (With KG = 1 the followers are the waves of query block 2p + 1.)
+    int lead_v = upper ? 0 : 1;
+    asm("" : "+v"(lead_v));
+    const bool lead = lead_v != 0;
+    auto second = [&](bool follower) { return PAIR && (KG == 1 ? follower : qb > qb0); };
+    issue_tile(k_slot0, rk_at(w0), kp);
+    issue_tile(v_slot0, rv_at(w0), vp);
+    issue_tile(k_slot0 + TL::BYTES, rk_at(w1), kp);
     wait_loads_and_sync();
-    Scores<BLOCK> sc;
-    compute_scores<BLOCK>(k_lds, qf, sc, fa);   // S(0)
-    mask_block(sc, w0);
-    Probs<BLOCK> pr;
-    if (lead) softmax_phase<BLOCK, RSUM>(sc, ws, pr, scale_log2, nullptr);   // P(0)
+    Scores<KTW> sc;
+    compute_scores<KTW>(k_lds, qf, sc, fa);   // S(0)
+    mask_block(sc, w0, second(upper));
+    Probs<KTW> pr;
+    if (lead) softmax_phase<KTW, RSUM>(sc, ws, pr, scale_log2, nullptr);   // P(0)
     __syncthreads();
     for (int j = 0; j < n; ++j) {
       // Word of step j+3 from the walk's LDS, read now and used at the end of
       // the step (the last word again past the end of the walk; a sparse
       // walk never passes WALK_CAP words, nb <= WALK_CAP).
-      const int g3 = min(j + 3, n - 1);
+      const int g3 = SUBS * min(j + 3, n - 1) + sub;
       const uint32_t w3v = walk.w[min(g3, WALK_CAP - 1)];
-      const StepLoads<BLOCK> sl{
+      const StepLoads sl{
           (uint32_t)__builtin_amdgcn_readfirstlane(k_slot0 + (uint32_t)(j & 1) * TL::BYTES),
           (uint32_t)__builtin_amdgcn_readfirstlane(v_slot0 + (uint32_t)((j + 1) & 1) * TL::BYTES),
           rk_at(w2), rv_at(w1), &kp, &vp};
@@ -784,29 +880,29 @@ __device__ __forceinline__ void attn_tile(
       const char* const vj = v_lds + (j & 1) * TL::BYTES;          // V(j)
       // half-period 2j
       if (lead) {
-        gemm_phase<BLOCK, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones, &sl);
-        mask_block(sc, w1);
+        gemm_phase<KTW, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones, &sl);
+        mask_block(sc, w1, second(false));
       } else {
-        softmax_phase<BLOCK, RSUM>(sc, ws, pr, scale_log2, &sl);
+        softmax_phase<KTW, RSUM>(sc, ws, pr, scale_log2, &sl);
       }
       __syncthreads();
       // half-period 2j+1
       if (lead) {
-        if (j + 1 < n) softmax_phase<BLOCK, RSUM>(sc, ws, pr, scale_log2, nullptr);
+        if (j + 1 < n) softmax_phase<KTW, RSUM>(sc, ws, pr, scale_log2, nullptr);
       } else {
-        gemm_phase<BLOCK, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones, nullptr);
-        mask_block(sc, w1);
+        gemm_phase<KTW, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones, nullptr);
+        mask_block(sc, w1, second(true));
       }
       wait_loads_and_sync();
       w1 = w2;
       w2 = SPARSE || g3 < WALK_CAP ? (uint32_t)__builtin_amdgcn_readfirstlane((int)w3v)
-                                   : (uint32_t)(nb - 1 - g3) | 0xC0000000u;
+                                   : dense_word(g3);
     }
     __syncthreads();
   }
 
-  // Every wave holds whole rows: O / l, rounded to bf16.  The l tile holds
-  // row c in register 0 of lane c and row c + 16 in register 1 (c < 16).
+  // Row sums: the l tile holds row c in register 0 of lane c and row c + 16 in
+  // register 1 (c < 16); the VALU form's halves are in lanes l and l^32.
   float lsum;
   if constexpr (RSUM == RSUM_MFMA) {
     const float r0s = __shfl(ws.l[0], li), r1s = __shfl(ws.l[1], li & 15);
@@ -815,9 +911,12 @@ __device__ __forceinline__ void attn_tile(
     const float lpart = ws.l0 + ws.l1;
     lsum = lpart + __shfl_xor(lpart, 32);
   }
-  const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-  if (qrow < N) {
-    __bf16* orow = oh + (int64_t)qrow * o_st;
+  __bf16* const orow = oh + (int64_t)qrow * o_st;
+  if constexpr (KG > 1) {
+    combine_groups<KG>(lds, ws, lsum, orow, qrow < N, wave, lane);
+  } else if (qrow < N) {
+    // Every wave holds whole rows: O / l, rounded to bf16.
+    const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -831,8 +930,8 @@ __device__ __forceinline__ void attn_tile(
   }
 }
 
-// First tile and tile count of XCD x's share of `total` tiles: contiguous
-// shares, the first total % 8 of them one tile larger.
+// First item and item count of XCD x's share of `total` items: contiguous
+// shares, the first total % 8 of them one item larger.
 __device__ __forceinline__ int xcd_first(int x, int total) {
   const int per = total / 8, rem = total % 8;
   return x < rem ? x * (per + 1) : rem * (per + 1) + (x - rem) * per;
@@ -841,22 +940,29 @@ __device__ __forceinline__ int xcd_count(int x, int total) {
   return total / 8 + (x < total % 8 ? 1 : 0);
 }
 
-// Next tile for a workgroup on XCD `xcd`, or -1 when every tile is handed
-// out.  Tiles are dealt to the XCDs in contiguous shares; a workgroup takes
-// the next tile from the front of its own XCD's share and, once that share
-// is handed out, the last one left at the back of another XCD's share, so
-// XCDs that clock faster take on more tiles while each share is still
-// worked from its front by its own XCD (neighbouring tiles, whose key lists
-// overlap, stay together in that XCD's L2).  Counter word x holds in bits
-// 0..31 the takes from the front of share x and in bits 32..63 those from
-// its back; a take gets a tile iff the two counts before it sum to less
-// than the share's size, so each tile goes out once.  Every call makes at
-// most 8 atomic adds, so a workgroup's loop ends after at most total + 8
-// calls.
-__device__ __forceinline__ int fetch_tile(uint64_t* ctr, int xcd, int total) {
+// A launch's items are `whole` whole tiles, then `split` parts of the tiles
+// after them; an XCD's share is its share of the whole tiles followed by its
+// share of the parts.  Item i of share x:
+__device__ __forceinline__ int share_item(int x, int i, int whole, int split) {
+  const int w = xcd_count(x, whole);
+  return i < w ? xcd_first(x, whole) + i : whole + xcd_first(x, split) + (i - w);
+}
+
+// Next item for a workgroup on XCD `xcd`, or -1 when every item is handed
+// out.  Items are dealt to the XCDs in shares; a workgroup takes the next
+// item from the front of its own XCD's share and, once that share is handed
+// out, the last one left at the back of another XCD's share, so XCDs that
+// clock faster take on more items while each share is still worked from its
+// front by its own XCD (neighbouring tiles, whose key lists overlap, stay
+// together in that XCD's L2).  Counter word x holds in bits 0..31 the takes
+// from the front of share x and in bits 32..63 those from its back; a take
+// gets an item iff the two counts before it sum to less than the share's
+// size, so each item goes out once.  Every call makes at most 8 atomic adds,
+// so a workgroup's loop ends after at most items + 8 calls.
+__device__ __forceinline__ int fetch_item(uint64_t* ctr, int xcd, int whole, int split) {
   for (int d = 0; d < 8; ++d) {
     const int x = (xcd + d) % 8;
-    const uint64_t cnt = (uint64_t)xcd_count(x, total);
+    const uint64_t cnt = (uint64_t)(xcd_count(x, whole) + xcd_count(x, split));
     const uint64_t seen =
         __hip_atomic_load(&ctr[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((seen & 0xFFFFFFFFull) + (seen >> 32) >= cnt) continue;
@@ -864,7 +970,7 @@ __device__ __forceinline__ int fetch_tile(uint64_t* ctr, int xcd, int total) {
                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint64_t front = old & 0xFFFFFFFFull, back = old >> 32;
     if (front + back < cnt)
-      return xcd_first(x, total) + (d == 0 ? (int)front : (int)(cnt - 1 - back));
+      return share_item(x, d == 0 ? (int)front : (int)(cnt - 1 - back), whole, split);
   }
   return -1;
 }
@@ -879,36 +985,48 @@ struct KArgs {
   int64_t q_sh, q_st, k_sh, k_st, v_sh, v_st, o_sh, o_st;
   const int32_t* row_ptr;
   const uint32_t* rows;
-  uint64_t* counters;
-  int32_t H, N, nb, P;
+  uint64_t* counters;        // null: one item per workgroup
+  int32_t N, nb, P;
+  int32_t per_head;          // whole tiles of a head
+  int32_t whole, split;      // items (share_item)
   float scale_log2;
 };
 
-template <int BLOCK, int MODE>
-__device__ __forceinline__ void attn_tile_args(char* lds, WalkLds& walk, int tile,
+template <int BLOCK, int MODE, int KG>
+__device__ __forceinline__ void attn_tile_args(char* lds, WalkLds& walk, int head, int row0,
                                                const KArgs& a) {
-  attn_tile<BLOCK, MODE>(lds, walk, tile, a.q, a.k, a.v, a.o, a.q_sh, a.q_st, a.k_sh, a.k_st,
-                         a.v_sh, a.v_st, a.o_sh, a.o_st, a.H, a.N, a.nb, a.row_ptr,
-                         a.rows, a.P, a.scale_log2);
+  attn_tile<BLOCK, MODE, KG>(lds, walk, head, row0, a.q, a.k, a.v, a.o, a.q_sh, a.q_st, a.k_sh,
+                             a.k_st, a.v_sh, a.v_st, a.o_sh, a.o_st, a.N, a.nb, a.row_ptr,
+                             a.rows, a.P, a.scale_log2);
 }
 
-// Persistent workgroups, at most one per CU, take tiles until all are done
-// (fetch_tile), through the launch's own counters, zeroed by
-// zero_counters_kernel just before on the same stream.
-template <int BLOCK, int MODE>
-__global__ __launch_bounds__(Tile<BLOCK>::NT) void attn_fwd_kernel(const KArgs args) {
-  __shared__ __attribute__((aligned(1024))) char lds[4 * Tile<BLOCK>::BYTES];
+// Persistent workgroups, at most one per CU, take items until all are done
+// (fetch_item), through the launch's own counters, zeroed by
+// zero_counters_kernel just before on the same stream; without counters
+// there is a workgroup for every item (all whole or all split).  Whole tiles
+// run with KGW key groups, the parts of split ones with KGS (KGS / KGW parts
+// per tile).
+template <int BLOCK, int MODE, int KGW, int KGS>
+__global__ __launch_bounds__(Tile::NT) void attn_fwd_kernel(const KArgs args) {
+  __shared__ __attribute__((aligned(1024))) char lds[4 * Tile::BYTES];
   __shared__ WalkLds walk;
-  __shared__ int next_tile;
-  const int total = (args.nb + 1) / 2 * args.H;
+  __shared__ int next_item;
+  constexpr int PARTS = KGS / KGW;
   // Workgroups are dispatched round-robin over the 8 XCDs.
   const int xcd = blockIdx.x % 8;
   for (;;) {
-    if (threadIdx.x == 0) next_tile = fetch_tile(args.counters, xcd, total);
-    __syncthreads();
-    const int tile = __builtin_amdgcn_readfirstlane(next_tile);
-    __syncthreads();   // every wave has read next_tile before it is rewritten
-    if (tile < 0) break;
+    int item;
+    if (args.counters) {
+      if (threadIdx.x == 0)
+        next_item = fetch_item(args.counters, xcd, args.whole, args.split);
+      __syncthreads();
+      item = __builtin_amdgcn_readfirstlane(next_item);
+      __syncthreads();   // every wave has read next_item before it is rewritten
+      if (item < 0) break;
+    } else {
+      item = __builtin_amdgcn_readfirstlane(
+          share_item(xcd, (int)(blockIdx.x / 8), args.whole, args.split));
+    }
     // The arguments are the first kernel argument; an offset the compiler
     // cannot see to be zero makes every tile load them afresh (scalar
     // loads), so they are not live across tiles.
@@ -916,7 +1034,24 @@ __global__ __launch_bounds__(Tile<BLOCK>::NT) void attn_fwd_kernel(const KArgs a
     asm volatile("" : "+v"(zero));
     zero = __builtin_amdgcn_readfirstlane(zero);
     const KArgs* ap = (const KArgs*)((const char*)__builtin_amdgcn_kernarg_segment_ptr() + zero);
-    attn_tile_args<BLOCK, MODE>(lds, walk, tile, *ap);
+    // Tiles of a head go last to first: rows that attend every key block (text
+    // tokens, placed after the video tokens) are the longest tiles, and taking
+    // them first keeps them out of the grid's tail (each row's key blocks are
+    // then walked in descending order, which keeps neighbouring workgroups'
+    // shared blocks in L2).
+    if (item < ap->whole) {
+      const int p = ap->per_head - 1 - item % ap->per_head;
+      attn_tile_args<BLOCK, MODE, KGW>(lds, walk, item / ap->per_head,
+                                       p * Split<KGW>::ROWS, *ap);
+    } else if constexpr (PARTS > 1) {
+      const int u = item - ap->whole;
+      const int tile = ap->whole + u / PARTS;
+      const int p = ap->per_head - 1 - tile % ap->per_head;
+      const int row0 = p * Split<KGW>::ROWS + (PARTS - 1 - u % PARTS) * Split<KGS>::ROWS;
+      if (row0 < ap->N)
+        attn_tile_args<BLOCK, MODE, KGS>(lds, walk, tile / ap->per_head, row0, *ap);
+    }
+    if (!args.counters) break;
   }
 }
 
@@ -939,13 +1074,62 @@ int cu_count() {
   return n;
 }
 
-template <int BLOCK, int MODE>
-hipError_t launch_t(const AttnArgs& a, hipStream_t stream) {
+// How a launch's tiles are split (see Split): `whole` tiles of 256 / kgw rows,
+// the rest in parts of 256 / kgs rows.
+struct Plan {
+  int kgw, kgs, whole;
+};
+
+int tiles_of(const AttnArgs& a, int kg) {
+  const int rows = 256 / kg;
+  return (int)(((int64_t)a.n_tokens + rows - 1) / rows) * a.heads;
+}
+
+// Rounds of whole tiles that the launch takes, by the plan: a CU works one
+// tile at a time, so a last round that is nearly empty costs as much as a full
+// one, and a launch of fewer tiles than CUs leaves CUs idle.  Splitting tiles
+// over the key groups of a workgroup (Split) gives more, shorter items: a
+// 128-row item takes 0.60 of a 256-row tile's time and a 64-row one 0.42 (not
+// 0.5 and 0.25: each K/V tile brought into LDS serves fewer rows; measured with
+// every CU busy, Wan-1.3B 1x and 6x: 4.50 and 29.2 ms whole, 5.44 and 34.1 ms in
+// 128-row items, 7.48 and 42.7 ms in 64-row items; with 64-token blocks 10.8
+// against 13.7 ms).  So whole tiles fill all rounds but the last one or two,
+// and what remains is split if that ends earlier.
+Plan make_plan(const AttnArgs& a, int block, int cus) {
+  struct Kind { int kgw, kgs; double whole, part; };
+  static const Kind kinds128[] = {{1, 2, 1.0, 0.60}, {1, 4, 1.0, 0.42}, {2, 4, 0.60, 0.42}};
+  static const Kind kinds64[] = {{2, 4, 1.0, 0.64}};
+  const Kind* const kinds = block == 128 ? kinds128 : kinds64;
+  const int nkinds = block == 128 ? 3 : 1;
+  const int tiles0 = tiles_of(a, kinds[0].kgw);
+  Plan best{kinds[0].kgw, kinds[0].kgs, tiles0};
+  // A split has to gain 1% to be taken.
+  double best_cost = 0.99 * ((tiles0 + cus - 1) / cus);
+  for (int i = 0; i < nkinds; ++i) {
+    const Kind& k = kinds[i];
+    const int tiles = tiles_of(a, k.kgw), rounds = tiles / cus;
+    for (int w = rounds; w >= 0 && w >= rounds - 1; --w) {
+      const int64_t parts = (int64_t)(tiles - w * cus) * (k.kgs / k.kgw);
+      const double cost = w * k.whole + (double)((parts + cus - 1) / cus) * k.part;
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = Plan{k.kgw, k.kgs, w * cus};
+      }
+    }
+  }
+  return best;
+}
+
+template <int BLOCK, int MODE, int KGW, int KGS>
+hipError_t launch_t(const AttnArgs& a, int whole, hipStream_t stream) {
   const float scale_log2 = 1.4426950408889634f / __builtin_sqrtf((float)D);
-  const int tiles = (a.n_blocks + 1) / 2 * a.heads;
-  // One persistent workgroup per CU (each takes 160 KB of LDS at BLOCK =
-  // 128, so one fits a CU), or one per tile when there are fewer tiles.
-  const int grid = tiles < cu_count() ? tiles : cu_count();
+  const int per_head = (int)(((int64_t)a.n_tokens + Split<KGW>::ROWS - 1) / Split<KGW>::ROWS);
+  const int tiles = per_head * a.heads;
+  const int split = (tiles - whole) * (KGS / KGW);
+  const int items = whole + split;
+  // One persistent workgroup per CU (each takes 160 KB of LDS, so one fits a
+  // CU), or one per item when there are fewer items.
+  const int grid = items < cu_count() ? items : cu_count();
   KArgs k;
   k.q = (const __bf16*)a.q;
   k.k = (const __bf16*)a.k;
@@ -955,11 +1139,15 @@ hipError_t launch_t(const AttnArgs& a, hipStream_t stream) {
   k.v_sh = a.v_sh; k.v_st = a.v_st; k.o_sh = a.o_sh; k.o_st = a.o_st;
   k.row_ptr = a.row_ptr;
   k.rows = a.rows;
-  k.counters = a.counters;
-  k.H = a.heads; k.N = a.n_tokens; k.nb = a.n_blocks; k.P = a.frame_tokens;
+  k.counters = items <= grid && (whole == 0 || split == 0) ? nullptr : a.counters;
+  k.N = a.n_tokens; k.nb = a.n_blocks; k.P = a.frame_tokens;
+  k.per_head = per_head;
+  k.whole = whole;
+  k.split = split;
   k.scale_log2 = scale_log2;
-  hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, stream, a.counters);
-  hipLaunchKernelGGL((attn_fwd_kernel<BLOCK, MODE>), dim3(grid), dim3(Tile<BLOCK>::NT), 0,
+  if (k.counters)
+    hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, stream, a.counters);
+  hipLaunchKernelGGL((attn_fwd_kernel<BLOCK, MODE, KGW, KGS>), dim3(grid), dim3(Tile::NT), 0,
                      stream, k);
   return hipGetLastError();
 }
@@ -980,14 +1168,21 @@ hipError_t launch_attention(const AttnArgs& a, int32_t block, AttnMode mode,
     d.rows = nullptr;
     return launch_attention(d, block, ATTN_BLOCK, stream);
   }
-  if (block == 128) {
-    if (mode == ATTN_EXACT) return launch_t<128, ATTN_EXACT>(a, stream);
-    if (mode == ATTN_BLOCK) return launch_t<128, ATTN_BLOCK>(a, stream);
-    return launch_t<128, ATTN_DENSE>(a, stream);
+  if (mode == ATTN_DENSE)
+    return block == 128 ? launch_t<128, ATTN_DENSE, 1, 1>(a, tiles_of(a, 1), stream)
+                        : launch_t<64, ATTN_DENSE, 2, 2>(a, tiles_of(a, 2), stream);
+  const Plan p = make_plan(a, block, cu_count());
+  if (block == 64)
+    return mode == ATTN_EXACT ? launch_t<64, ATTN_EXACT, 2, 4>(a, p.whole, stream)
+                              : launch_t<64, ATTN_BLOCK, 2, 4>(a, p.whole, stream);
+  if (mode == ATTN_EXACT) {
+    if (p.kgw == 2) return launch_t<128, ATTN_EXACT, 2, 4>(a, p.whole, stream);
+    if (p.kgs == 4) return launch_t<128, ATTN_EXACT, 1, 4>(a, p.whole, stream);
+    return launch_t<128, ATTN_EXACT, 1, 2>(a, p.whole, stream);
   }
-  if (mode == ATTN_EXACT) return launch_t<64, ATTN_EXACT>(a, stream);
-  if (mode == ATTN_BLOCK) return launch_t<64, ATTN_BLOCK>(a, stream);
-  return launch_t<64, ATTN_DENSE>(a, stream);
+  if (p.kgw == 2) return launch_t<128, ATTN_BLOCK, 2, 4>(a, p.whole, stream);
+  if (p.kgs == 4) return launch_t<128, ATTN_BLOCK, 1, 4>(a, p.whole, stream);
+  return launch_t<128, ATTN_BLOCK, 1, 2>(a, p.whole, stream);
 }
 
 }  // namespace lvsa
