@@ -76,9 +76,9 @@ namespace lvsa {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int D = 128;             // head_dim
@@ -93,25 +93,38 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base,
                                            bytes, 0x00020000);
 }
 
-__device__ __forceinline__ float pair_max(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x),
-                                            __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+// Largest of x0 (and of x1) over the four lanes that hold one query row (l,
+// l^16, l^32, l^48); every lane gets both results.  With 16-lane groups
+// [0 1 2 3], permlane16_swap(a, b) gives [a0 b0 a2 b2] and [a1 b1 a3 b3], and
+// permlane32_swap(a, b) gives [a0 a1 b0 b1] and [a2 a3 b2 b3].
+__device__ __forceinline__ void row_max(float& x0, float& x1) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x0), __float_as_uint(x1),
+                                                  false, false);
+  const float y = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));   // x0 x1 x0 x1
+  const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false,
+                                                  false);
+  const float z = fmaxf(__uint_as_float(t[0]), __uint_as_float(t[1]));
+  const auto u = __builtin_amdgcn_permlane16_swap(__float_as_uint(z), __float_as_uint(z), false,
+                                                  false);
+  x0 = __uint_as_float(u[0]);
+  x1 = __uint_as_float(u[1]);
 }
 
 // LDS tile layout ("slabs").  A BLOCK x 128 tile (one key block) is stored
 // as 4 slabs of 32 columns; a slab row is 64 bytes (4 chunks of 16 bytes) and
 // rows follow each other, so tile byte (slab, row, chunk) =
 // slab*BLOCK*64 + row*64 + chunk*16.
-// The chunk is XORed with x(row) = (row/4) % 4.  With 64 banks of 4 bytes:
-//   - ds_read_b128 (served 16 lanes at a time) reads 16 consecutive rows at
-//     one logical chunk: 4 rows share a bank window and the XOR separates them;
-//   - ds_read_b64_tr_b16 (served 32 lanes at a time) reads 4 consecutive rows
-//     x 4 chunks, i.e. 256 contiguous bytes.
+// The chunk is XORed with x(row) = -(row/4) mod 4.  With 64 banks of 4 bytes:
+//   - ds_read_b128 is served 16 lanes at a time, lanes 0-3, 12-15 and 20-27
+//     together (then 4-11, 16-19 and 28-31; the same from lane 32 on): rows
+//     0-3 and 12-15 at one logical chunk c and rows 4-11 at c ^ 1, which x
+//     sends to four different bank quarters;
+//   - ds_read_b64_tr_b16 (served 32 lanes at a time) reads 8 consecutive rows
+//     x 2 chunks of a 32-byte half: rows 4..7 take the other half's banks.
 // Both are free of bank conflicts, and every fragment address an unrolled loop
-// needs is one of two per-lane bases plus an immediate offset.
+// needs is one of three per-lane bases plus an immediate offset.
 constexpr int SLAB_ROW = 64;
-__device__ __forceinline__ int xsw(int row) { return (row >> 2) & 3; }
+__device__ __forceinline__ int xsw(int row) { return -(row >> 2) & 3; }
 
 struct Tile {
   static constexpr int NW = 8;                      // waves
@@ -132,7 +145,7 @@ struct Split {
   static constexpr int ROWS = 256 / KG;             // query rows per tile
   static constexpr int NRG = 8 / KG;                // waves per key group
   static constexpr int NK = Tile::KEYS / KG;        // keys per wave and step
-  static constexpr int KTW = NK / 32;               // 32-key tiles per wave and step
+  static constexpr int NU = NK / 32;                // 32-key groups per wave and step
 };
 
 // One wave load (1 KiB) of a K or V tile into LDS at byte address lds_dst:
@@ -145,13 +158,13 @@ struct Split {
 // wait state gfx9 needs between an SALU write of M0 and an LDS-DMA
 // instruction (the compiler cannot see into the statement to add it).
 __device__ __forceinline__ void issue_load(uint32_t lds_dst, __amdgpu_buffer_rsrc_t rsrc,
-                                           uint32_t voff) {
+                                           uint32_t voff, uint32_t soff) {
   asm volatile(
       "s_mov_b32 m0, %0\n\t"
       "s_nop 0\n\t"
-      "buffer_load_dwordx4 %1, %2, 0 offen lds"
+      "buffer_load_dwordx4 %1, %2, %3 offen lds"
       :
-      : "s"(lds_dst), "v"(voff), "s"(rsrc)
+      : "s"(lds_dst), "v"(voff), "s"(rsrc), "s"(soff)
       : "memory", "m0");
 }
 
@@ -170,12 +183,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const __bf16* head_b
 
 // Per-wave load plan: wave w's load j of a tile fills tile bytes
 // 1024*(w + NW*j): slab j, rows 16*w + lane/4, physical chunk lane%4, which
-// holds logical chunk (lane%4) ^ x(row) = (lane%4) ^ (lane/16).  Global
+// holds logical chunk (lane%4) ^ x(row).  Global
 // offset: lane_off plus 64*j; LDS offset: lds_w plus 1024*NW*j.  With BLOCK =
 // 64 a step's tile is two key blocks, rows 0..63 and 64..127, and the
 // resource that waves 4..7 load through starts at the second one.
 struct LoadPlan {
-  uint32_t lane_off;   // (16*(w % (BLOCK/16)) + lane/4)*row_bytes + 16*((lane%4) ^ (lane/16))
+  uint32_t lane_off;   // (16*(w % (BLOCK/16)) + lane/4)*row_bytes + 16*((lane%4) ^ x(lane/4))
   uint32_t lds_w;      // 1024*w (uniform)
 };
 
@@ -183,7 +196,7 @@ template <int BLOCK>
 __device__ __forceinline__ LoadPlan load_plan(uint32_t row_bytes, int wave, int lane) {
   LoadPlan lp;
   lp.lane_off = (uint32_t)(16 * (wave % (BLOCK / 16)) + lane / 4) * row_bytes +
-                16u * (uint32_t)((lane % 4) ^ (lane / 16));
+                16u * (uint32_t)((lane % 4) ^ xsw(lane / 4));
   lp.lds_w = (uint32_t)__builtin_amdgcn_readfirstlane(1024u * (uint32_t)wave);
   return lp;
 }
@@ -192,7 +205,7 @@ __device__ __forceinline__ void issue_tile(uint32_t lds, __amdgpu_buffer_rsrc_t 
                                            const LoadPlan& lp) {
 #pragma unroll
   for (int j = 0; j < Tile::LOADS; ++j)
-    issue_load(lds + lp.lds_w + 1024u * Tile::NW * j, rsrc, lp.lane_off + 64u * j);
+    issue_load(lds + lp.lds_w + 1024u * Tile::NW * j, rsrc, lp.lane_off, 64u * j);
 }
 
 // The loads of one pipeline step: the next K tile and the next V tile, spread
@@ -208,10 +221,10 @@ struct StepLoads {
 
 __device__ __forceinline__ void issue_step_load(const StepLoads& sl, int i) {
   if (i < Tile::LOADS)
-    issue_load(sl.k_dst + sl.kp->lds_w + 1024u * Tile::NW * i, sl.rk, sl.kp->lane_off + 64u * i);
+    issue_load(sl.k_dst + sl.kp->lds_w + 1024u * Tile::NW * i, sl.rk, sl.kp->lane_off, 64u * i);
   else
     issue_load(sl.v_dst + sl.vp->lds_w + 1024u * Tile::NW * (i - Tile::LOADS), sl.rv,
-               sl.vp->lane_off + 64u * (i - Tile::LOADS));
+               sl.vp->lane_off, 64u * (i - Tile::LOADS));
 }
 
 __device__ __forceinline__ void wait_loads_and_sync() {
@@ -219,93 +232,105 @@ __device__ __forceinline__ void wait_loads_and_sync() {
   __syncthreads();
 }
 
-template <int KTW>
+// Scores of the wave's 32 query rows (two tiles of 16) against its keys, 16
+// keys per tile: lane l holds query rows l%16 of both tiles and keys
+// 16*kt + 4*(l/16) + r.
+template <int NU>
 struct Scores {
-  f32x16 s[KTW];   // one 32-key tile each
+  f32x4 s[2 * NU][2];   // [key tile][query tile]
 };
 
 // Per-lane LDS byte offsets (within a tile) of the K and V fragments.
 struct FragAddr {
-  uint32_t k_even, k_odd;   // K rows of this lane, d-steps 2t / 2t+1
-  uint32_t v_lo, v_hi;      // V rows for k-slots 0..3 / 4..7 (transposing read)
+  uint32_t k;               // K row of this lane
+  uint32_t v_even, v_odd;   // V row, d tiles 2t / 2t+1 (transposing read)
 };
 
 // `key0`: the first key of the wave's share of the step.
 __device__ __forceinline__ FragAddr frag_addr(int lane, int key0) {
-  const int hl = lane / 32, li = lane % 32;
+  const int g = lane / 16, sl = lane % 16;
   FragAddr f;
-  // K: row 32*kt + li, d = 16*stp + 8*hl: slab stp/2, logical chunk
-  // 2*(stp%2) + hl.  x(row) = (li/4)%4 for every kt.
-  const int krow = key0 + li;
-  const int kx = xsw(li);
-  f.k_even = krow * SLAB_ROW + ((hl ^ kx) * 16);
-  f.k_odd = krow * SLAB_ROW + (((2 + hl) ^ kx) * 16);
+  // K: row 16*kt + sl, d = 32*stp + 8*g: slab stp, logical chunk g.
+  f.k = (key0 + sl) * SLAB_ROW + ((g ^ xsw(sl)) * 16);
   // V: the transposing read gives lane (group g = lane/16, j = lane%16)
   // element e of the group's chunk 4e + j/4, entry j%4.  Source lane
-  // sl = 4e + q points at V row (key e of its half: 4*(g/2) + sl/4) and
-  // columns 16*(g%2) + 4q .. +3 of the slab (logical chunk 2*(g%2) + q/2,
-  // byte half q%2).  Rows +8 hold k-slots 4..7.
-  const int g = lane / 16, sl = lane % 16;
-  const int vrow = 4 * (g / 2) + sl / 4;
-  const int lc = 2 * (g % 2) + (sl % 4) / 2;
-  const int half = (sl % 2) * 8;
-  f.v_lo = (key0 + vrow) * SLAB_ROW + ((lc ^ xsw(vrow)) * 16) + half;
-  f.v_hi = (key0 + vrow + 8) * SLAB_ROW + ((lc ^ xsw(vrow + 8)) * 16) + half;
+  // sl = 4e + q points at V row (key 4g + e) and columns 4q .. 4q+3 of the 16
+  // of the d tile (slab dt/2, logical chunk 2*(dt%2) + q/2, byte half q%2).
+  const int vrow = 4 * g + sl / 4;
+  f.v_even = (key0 + vrow) * SLAB_ROW + ((((sl % 4) / 2) ^ xsw(vrow)) * 16) + (sl % 2) * 8;
+  f.v_odd = f.v_even ^ 32u;
   return f;
 }
 
+// K fragment (16 keys x 32 d) and V^T fragment (16 d x 32 keys).  k-slot e < 4
+// of lane group g is key 4g + e of the first 16, e >= 4 the same of the second
+// 16: the order in which P's lanes hold their keys.
+__device__ __forceinline__ bf16x8 k_frag(const char* lds_k, const FragAddr& fa, int kt, int stp) {
+  return *(const bf16x8*)(lds_k + fa.k + stp * Tile::SLAB + kt * 16 * SLAB_ROW);
+}
+__device__ __forceinline__ i16x4 v_half(const char* lds_v, const FragAddr& fa, int dt, int u,
+                                        int half) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (lds_i16x4*)(lds_v + ((dt & 1) ? fa.v_odd : fa.v_even) + (dt / 2) * Tile::SLAB +
+                   (u * 32 + half * 16) * SLAB_ROW));
+}
+__device__ __forceinline__ bf16x8 join(i16x4 lo, i16x4 hi) {
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+__device__ __forceinline__ bf16x8 v_frag(const char* lds_v, const FragAddr& fa, int dt, int u) {
+  return join(v_half(lds_v, fa, dt, u, 0), v_half(lds_v, fa, dt, u, 1));
+}
+
 // S^T = K Q^T for the wave's keys of one step (K tile at lds_k).
-template <int KTW>
-__device__ __forceinline__ void compute_scores(const char* lds_k, const bf16x8 (&qf)[8],
-                                               Scores<KTW>& sc, const FragAddr& fa) {
+template <int NU>
+__device__ __forceinline__ void compute_scores(const char* lds_k, const bf16x8 (&qf)[4][2],
+                                               Scores<NU>& sc, const FragAddr& fa) {
 #pragma unroll
-  for (int kt = 0; kt < KTW; ++kt) {
-    f32x16 acc = f32x16{};
+  for (int kt = 0; kt < 2 * NU; ++kt) {
+    f32x4 acc[2] = {f32x4{}, f32x4{}};
 #pragma unroll
-    for (int stp = 0; stp < 8; ++stp) {
-      const uint32_t off = ((stp & 1) ? fa.k_odd : fa.k_even) +
-                           (stp / 2) * Tile::SLAB + kt * 32 * SLAB_ROW;
-      const bf16x8 a = *(const bf16x8*)(lds_k + off);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[stp], acc, 0, 0, 0);
+    for (int stp = 0; stp < 4; ++stp) {
+      const bf16x8 a = k_frag(lds_k, fa, kt, stp);
+#pragma unroll
+      for (int qt = 0; qt < 2; ++qt)
+        acc[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[stp][qt], acc[qt], 0, 0, 0);
     }
-    sc.s[kt] = acc;
+    sc.s[kt][0] = acc[0];
+    sc.s[kt][1] = acc[1];
   }
 }
 
 // Row sums l are kept one of two ways (RSUM): on the matrix core, as a
 // 16x16 MFMA accumulator that the GEMM phase adds each step's bf16 P into
-// (lane c < 16 holds rows c and c + 16), or on the VALU, as two partial sums
-// per lane of the fp32 probabilities of the lane's own keys that the softmax
-// phase adds into (lanes l and l^32 hold the two halves of a row's keys).
-// Timed interleaved on one board, the VALU form is 0.4-0.7% faster in the
-// block mode (four workloads), and slower in the dense mode (0.4-0.9%: long
-// walks) and in the token-exact mode (0.4%: its masking adds VALU work to the
-// same phases).
+// (register 0 of every lane holds its row's sum), or on the VALU, as a
+// partial sum per lane and query tile of the fp32 probabilities of the lane's
+// own keys that the softmax phase adds into (the four lanes of a row hold
+// its parts).
 enum RowSums { RSUM_MFMA = 0, RSUM_VALU = 1 };
 
 struct WaveState {
-  f32x16 o[4];   // O^T tiles [d tile]: d = 32*dt + C row
-  float m;       // running max (log2 domain), shared by lanes l, l^32
-  f32x4 l;       // RSUM_MFMA: row sums (16x16 C tile)
-  float l0, l1;  // RSUM_VALU: partial row sums of the lane's keys
+  f32x4 o[8][2];   // O^T tiles [d tile][query tile]: d = 16*dt + C row
+  float m[2];      // running max (log2 domain), the same in a row's four lanes
+  f32x4 lt[2];     // RSUM_MFMA: row sums
+  float l[2];      // RSUM_VALU: partial row sums of the lane's keys
 };
 
 // Keys at or past N (ragged last block) do not exist: their scores become
 // -inf.  `valid` = N - the wave's first key (at most 0: no key is valid).  Per
 // score one compare of a constant into VCC and one select, a scheduling
 // barrier every 4 scores so that few compare results are live at once.
-template <int KTW>
-__device__ __forceinline__ void mask_tail(Scores<KTW>& sc, int lane, int valid) {
-  const int hl = lane / 32;
-  if (valid < 32 * KTW) {
-    const int lim = valid - 4 * hl;   // key 4*hl + c is valid iff c < lim
+template <int NU>
+__device__ __forceinline__ void mask_tail(Scores<NU>& sc, int lane, int valid) {
+  if (valid < 32 * NU) {
+    const int lim = valid - 4 * (lane / 16);   // key 4*(lane/16) + c is valid iff c < lim
 #pragma unroll
-    for (int kt = 0; kt < KTW; ++kt)
+    for (int kt = 0; kt < 2 * NU; ++kt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-        const int c = 32 * kt + 8 * (r / 4) + (r % 4);
-        sc.s[kt][r] = c < lim ? sc.s[kt][r] : -__builtin_inff();
+      for (int r = 0; r < 4; ++r) {
+        if (r % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+        const bool ok = 16 * kt + r < lim;
+        sc.s[kt][0][r] = ok ? sc.s[kt][0][r] : -__builtin_inff();
+        sc.s[kt][1][r] = ok ? sc.s[kt][1][r] : -__builtin_inff();
       }
   }
 }
@@ -328,31 +353,34 @@ __device__ __forceinline__ void mask_tail(Scores<KTW>& sc, int lane, int valid) 
 // wave's 32 rows reaches `sec_from` (wave-uniform); the lane index is
 // recomputed here rather than held in a register through the loop.  `koff`
 // is the wave's first key within the key block.
-template <int BLOCK, int KTW>
-__device__ __forceinline__ void mask_exact(Scores<KTW>& sc, uint32_t pat, int kfirst,
+template <int BLOCK, int NU>
+__device__ __forceinline__ void mask_exact(Scores<NU>& sc, uint32_t pat, int kfirst,
                                            int valid, int sec_from, int koff) {
   if (pat != 0xFu || valid < BLOCK) {
     const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    const int hl = lane / 32, li = lane % 32;
-    const uint32_t bits = li >= sec_from ? pat >> 2 : pat;
-    const int klo = (bits & 1u) ? 0 : kfirst;
-    const int khi = (bits & 2u) ? valid : min(kfirst, valid);
-    const uint32_t shift = (uint32_t)(koff + 4 * hl - klo);
-    const uint32_t width = (uint32_t)max(khi - klo, 0);
 #pragma unroll
-    for (int kt = 0; kt < KTW; ++kt)
+    for (int qt = 0; qt < 2; ++qt) {
+      const uint32_t bits = 16 * qt + lane % 16 >= sec_from ? pat >> 2 : pat;
+      const int klo = (bits & 1u) ? 0 : kfirst;
+      const int khi = (bits & 2u) ? valid : min(kfirst, valid);
+      const uint32_t shift = (uint32_t)(koff + 4 * (lane / 16) - klo);
+      const uint32_t width = (uint32_t)max(khi - klo, 0);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-        const uint32_t c = (uint32_t)(32 * kt + 8 * (r / 4) + (r % 4));
-        sc.s[kt][r] = c + shift < width ? sc.s[kt][r] : -__builtin_inff();
-      }
+      for (int kt = 0; kt < 2 * NU; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (r == 0) __builtin_amdgcn_sched_barrier(0);
+          const uint32_t c = (uint32_t)(16 * kt + r);
+          sc.s[kt][qt][r] = c + shift < width ? sc.s[kt][qt][r] : -__builtin_inff();
+        }
+    }
   }
 }
 
-template <int KTW>
+// Probabilities in bf16: the B operands of the P V product.
+template <int NU>
 struct Probs {
-  bf16x8 p[KTW][2];   // [key tile][k-step half]
+  bf16x8 p[NU][2];   // [32-key group][query tile]
 };
 
 // Softmax phase of the ping-pong schedule: block j's scores (in `sc`) become
@@ -363,89 +391,91 @@ struct Probs {
 // loads to issue along the way.  Scheduling barriers every 8 scores keep the
 // compiler from hoisting many exponentials at once (S, P, O and Q already
 // fill the register file).
-template <int KTW, int RSUM>
-__device__ __forceinline__ void softmax_phase(const Scores<KTW>& sc, WaveState& st,
-                                              Probs<KTW>& pr, float scale_log2,
+template <int NU, int RSUM>
+__device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& st,
+                                              Probs<NU>& pr, float scale_log2,
                                               const StepLoads* sl) {
-  constexpr int NE = 16 * KTW;   // scores per lane
   constexpr int NLOADS = 2 * Tile::LOADS;
-  constexpr int LOAD_EVERY = NE / NLOADS >= 2 ? NE / NLOADS : 2;   // scores per load
+  constexpr int GROUPS = 4 * NU;                     // pairs of tiles of 4 scores
+  constexpr int PER = (NLOADS + GROUPS - 1) / GROUPS;
+  constexpr int EVERY = GROUPS > NLOADS ? GROUPS / NLOADS : 1;
   int issued = 0;
-  float mx = -__builtin_inff();
+  float mx[2];
 #pragma unroll
-  for (int e = 0; e < NE; ++e) mx = fmaxf(mx, sc.s[e / 16][e % 16]);
-  const float m = pair_max(mx) * scale_log2;
-  const bool raise = m > st.m + RESCALE_SLACK;
-  if (__builtin_amdgcn_ballot_w64(raise)) {
-    const float a = raise ? __builtin_amdgcn_exp2f(st.m - m) : 1.f;
-    st.m = raise ? m : st.m;
-    if constexpr (RSUM == RSUM_MFMA) {
-      // l tile: register 0 of lane c holds row c, register 1 row c + 16.
-      const float a16 = __shfl_xor(a, 16);
-      st.l[0] *= a;
-      st.l[1] *= a16;
-    } else {
-      st.l0 *= a;
-      st.l1 *= a;
-    }
+  for (int qt = 0; qt < 2; ++qt) {
+    mx[qt] = -__builtin_inff();
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) st.o[dt] *= a;
+    for (int kt = 0; kt < 2 * NU; ++kt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mx[qt] = fmaxf(mx[qt], sc.s[kt][qt][r]);
   }
-  const float msub = st.m == -__builtin_inff() ? 0.f : st.m;
+  row_max(mx[0], mx[1]);
+  const float m0 = mx[0] * scale_log2, m1 = mx[1] * scale_log2;
+  const bool raise0 = m0 > st.m[0] + RESCALE_SLACK, raise1 = m1 > st.m[1] + RESCALE_SLACK;
+  if (__builtin_amdgcn_ballot_w64(raise0 || raise1)) {
+    const float a[2] = {raise0 ? __builtin_amdgcn_exp2f(st.m[0] - m0) : 1.f,
+                        raise1 ? __builtin_amdgcn_exp2f(st.m[1] - m1) : 1.f};
+    st.m[0] = raise0 ? m0 : st.m[0];
+    st.m[1] = raise1 ? m1 : st.m[1];
 #pragma unroll
-  for (int el = 0; el < NE; el += 2) {
-    if (el % 8 == 0) __builtin_amdgcn_sched_barrier(0);
-    if (sl && el % LOAD_EVERY == 0 && issued < NLOADS) issue_step_load(*sl, issued++);
-    const float a =
-        __builtin_amdgcn_exp2f(__builtin_fmaf(sc.s[el / 16][el % 16], scale_log2, -msub));
-    const float b = __builtin_amdgcn_exp2f(
-        __builtin_fmaf(sc.s[(el + 1) / 16][(el + 1) % 16], scale_log2, -msub));
-    if constexpr (RSUM == RSUM_VALU) {
-      if (el % 4 == 0) st.l0 += a + b; else st.l1 += a + b;
+    for (int qt = 0; qt < 2; ++qt) {
+      if constexpr (RSUM == RSUM_MFMA) st.lt[qt][0] *= a[qt];
+      else st.l[qt] *= a[qt];
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) st.o[dt][qt] *= a[qt];
     }
-    const bf16x2 pk = {(__bf16)a, (__bf16)b};
-    pr.p[el / 16][(el % 16) / 8][el % 8] = pk[0];
-    pr.p[el / 16][(el % 16) / 8][el % 8 + 1] = pk[1];
   }
+  const float msub[2] = {st.m[0] == -__builtin_inff() ? 0.f : st.m[0],
+                         st.m[1] == -__builtin_inff() ? 0.f : st.m[1]};
+#pragma unroll
+  for (int u = 0; u < NU; ++u)
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int grp = 4 * u + 2 * qt + t;
+        if (t == 0) __builtin_amdgcn_sched_barrier(0);
+        if (sl && grp % EVERY == 0)
+          for (int i = 0; i < PER && issued < NLOADS; ++i) issue_step_load(*sl, issued++);
+#pragma unroll
+        for (int r = 0; r < 4; r += 2) {
+          const float a = __builtin_amdgcn_exp2f(
+              __builtin_fmaf(sc.s[2 * u + t][qt][r], scale_log2, -msub[qt]));
+          const float b = __builtin_amdgcn_exp2f(
+              __builtin_fmaf(sc.s[2 * u + t][qt][r + 1], scale_log2, -msub[qt]));
+          if constexpr (RSUM == RSUM_VALU) st.l[qt] += a + b;
+          const bf16x2 pk = {(__bf16)a, (__bf16)b};
+          pr.p[u][qt][4 * t + r] = pk[0];
+          pr.p[u][qt][4 * t + r + 1] = pk[1];
+        }
+      }
   if (sl)
     for (; issued < NLOADS; ++issued) issue_step_load(*sl, issued);
 }
 
 // GEMM phase of the ping-pong schedule: with RSUM_MFMA, l += the row sums of
-// P(j) (one 16x16x32 MFMA per 16-key step, `ones` its A operand); then
+// P(j) (one MFMA per 32 keys and query tile, `ones` its A operand); then
 // O += P(j) V(j) and S(j+1) = K(j+1) Q^T into `sc`, with K and V fragments
-// read AHEAD MFMAs early and the tile loads in `sl` (may be null) spread over
-// the phase.  The row-sum MFMAs come first: their operands are already in
-// registers, so they run while the first fragments arrive from LDS (0.2-1.2%
-// faster than after P V, interleaved on one board).
-template <int KTW, int RSUM>
+// read AHEAD fragments early and the tile loads in `sl` (may be null) spread
+// over the phase.  The row-sum MFMAs come first: their operands are already in
+// registers, so they run while the first fragments arrive from LDS.
+template <int NU, int RSUM>
 __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
-                                           const bf16x8 (&qf)[8], Scores<KTW>& sc,
-                                           const Probs<KTW>& pr, WaveState& st,
+                                           const bf16x8 (&qf)[4][2], Scores<NU>& sc,
+                                           const Probs<NU>& pr, WaveState& st,
                                            const FragAddr& fa, const bf16x8& ones,
                                            const StepLoads* sl) {
-  constexpr int NS = 8 * KTW;   // S MFMAs: (key tile, d-step)
-  constexpr int NP = 8 * KTW;   // PV fragments: (d tile, key tile, k-step half)
+  constexpr int NS = 8 * NU;   // K fragments: (key tile, d-step)
+  constexpr int NP = 8 * NU;   // V fragments: (d tile, 32-key group)
   constexpr int NF = NS + NP;
-  constexpr int AHEAD = 3;
+  constexpr int AHEAD = 6;
   constexpr int NLOADS = 2 * Tile::LOADS;
-  // Fragment i < NP: V^T, d tile i/(2*KTW), key tile (i/2)%KTW, k-step half
-  // i%2.  Fragment NP + f: K, key tile f/8, d-step f%8.  MFMAs on one
-  // accumulator follow each other, and P(j) (with its row sums) is done
-  // before S(j+1) is produced, so the two are never live together.
+  // Fragment i < NP: V^T, d tile i/NU, key group i%NU.  Fragment NP + f: K, key
+  // tile f/4, d-step f%4.  P(j) (with its row sums) is done before S(j+1) is
+  // produced, so the two are never live together.
   auto frag = [&](int i) -> bf16x8 {
-    if (i >= NP) {
-      const int f = i - NP;
-      const int kt = f / 8, stp = f % 8;
-      const uint32_t off = ((stp & 1) ? fa.k_odd : fa.k_even) + (stp / 2) * Tile::SLAB +
-                           kt * 32 * SLAB_ROW;
-      return *(const bf16x8*)(lds_k + off);
-    }
-    const int dt = i / (2 * KTW), kt = (i / 2) % KTW, c = i % 2;
-    const uint32_t off = dt * Tile::SLAB + (32 * kt + 16 * c) * SLAB_ROW;
-    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(lds_v + fa.v_lo + off));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(lds_v + fa.v_hi + off));
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    return i < NP ? v_frag(lds_v, fa, i / NU, i % NU)
+                  : k_frag(lds_k, fa, (i - NP) / 4, (i - NP) % 4);
   };
   bf16x8 fr[NF];
 #pragma unroll
@@ -453,28 +483,57 @@ __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (RSUM == RSUM_MFMA) {
 #pragma unroll
-    for (int kt2 = 0; kt2 < KTW; ++kt2)
+    for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-      for (int c2 = 0; c2 < 2; ++c2) {
-        st.l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pr.p[kt2][c2], st.l, 0, 0, 0);
+      for (int u = 0; u < NU; ++u) {
+        st.lt[qt] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pr.p[u][qt], st.lt[qt], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
   }
-#pragma unroll
-  for (int i = 0; i < NF; ++i) {
-    if (i + AHEAD < NF) fr[i + AHEAD] = frag(i + AHEAD);
-    if (sl && i % (NF / NLOADS) == 0) issue_step_load(*sl, i / (NF / NLOADS));
-    if (i < NP) {
-      const int dt = i / (2 * KTW), kt = (i / 2) % KTW, c = i % 2;
-      st.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], pr.p[kt][c], st.o[dt], 0, 0, 0);
-    } else {
-      const int f = i - NP;
-      const int kt = f / 8, stp = f % 8;
-      sc.s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], qf[stp],
-                                                         stp == 0 ? f32x16{} : sc.s[kt], 0, 0, 0);
+  // What MFMA m of the phase's 2 * NF carries along: a fragment read at every
+  // second one, the tile loads evenly spread.
+  i16x4 lo = i16x4{};
+  auto carry = [&](int m) {
+    const int i = m / 2 + AHEAD;
+    if (i < NF) {
+      if (i >= NP) {
+        if (m % 2 == 0) fr[i] = frag(i);
+      } else if (m % 2 == 0) {
+        lo = v_half(lds_v, fa, i / NU, i % NU, 0);
+      } else {
+        fr[i] = join(lo, v_half(lds_v, fa, i / NU, i % NU, 1));
+      }
     }
-    __builtin_amdgcn_sched_barrier(0);
-  }
+    if (sl && m % (2 * NF / NLOADS) == 0) issue_step_load(*sl, m / (2 * NF / NLOADS));
+  };
+  // The fragments of one accumulator pair (NU for a d tile, 4 for a key tile)
+  // one after the other into the first query tile's accumulator, then in the
+  // other order into the second's.
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+      for (int i = 0; i < NU; ++i) {
+        const int u = qt ? NU - 1 - i : i;
+        carry((2 * dt + qt) * NU + i);
+        st.o[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[dt * NU + u], pr.p[u][qt],
+                                                               st.o[dt][qt], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+  for (int kt = 0; kt < 2 * NU; ++kt)
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int stp = qt ? 3 - i : i;
+        carry(2 * NP + (2 * kt + qt) * 4 + i);
+        sc.s[kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            fr[NP + 4 * kt + stp], qf[stp][qt], i == 0 ? f32x4{} : sc.s[kt][qt], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 }
 
 // LDS of the merged walk: the step words of the tile's pair of query blocks
@@ -612,66 +671,68 @@ __device__ __forceinline__ int32_t single_row(WalkLds& L, const uint32_t* __rest
 }
 
 // Combines the key groups' partial results (KG > 1) and stores the tile's
-// rows: each of the KG waves that hold the same rows keeps 4 / KG of the four
+// rows: each of the KG waves that hold the same rows keeps 8 / KG of the eight
 // d tiles and takes the others' parts of them through LDS.  With m = max m_g,
 // O = sum_g 2^(m_g - m) O_g and l = sum_g 2^(m_g - m) l_g, added in the order
 // of the groups.  `xch`: the tile buffers, idle here; wave w's part of d tile
-// dt is the 4 KB at 4096*(4*w + dt), and the slot of a d tile the wave keeps
+// dt is the 2 KB at 2048*(8*w + dt), and the slot of a d tile the wave keeps
 // holds its rows' (m, l).
 template <int KG>
-__device__ __forceinline__ void combine_groups(char* xch, WaveState& st, float lsum,
-                                               __bf16* orow, bool row_ok, int wave, int lane) {
+__device__ __forceinline__ void combine_groups(char* xch, WaveState& st, const float (&lsum)[2],
+                                               __bf16* oh, int64_t o_st, int qrow, int N,
+                                               int wave, int lane) {
   using SP = Split<KG>;
-  constexpr int KEEP = 4 / KG;
+  constexpr int KEEP = 8 / KG;
   const int rg = wave % SP::NRG, kg = wave / SP::NRG;
-  const int li = lane % 32, hl = lane / 32;
-  auto slot = [&](int w, int dt) { return xch + 4096 * (4 * w + dt); };
+  auto slot = [&](int w, int dt) { return xch + 2048 * (8 * w + dt); };
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt) {
+  for (int dt = 0; dt < 8; ++dt) {
     if (dt / KEEP == kg) continue;
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
-      *(f32x4*)(slot(wave, dt) + 1024 * a + 16 * lane) =
-          f32x4{st.o[dt][4 * a], st.o[dt][4 * a + 1], st.o[dt][4 * a + 2], st.o[dt][4 * a + 3]};
+    for (int qt = 0; qt < 2; ++qt)
+      *(f32x4*)(slot(wave, dt) + 1024 * qt + 16 * lane) = st.o[dt][qt];
   }
-  if (hl == 0) {
-    float* const ml = (float*)(slot(wave, kg * KEEP) + 8 * li);
-    ml[0] = st.m;
-    ml[1] = lsum;
+  if (lane < 16) {
+    float* const ml = (float*)(slot(wave, kg * KEEP) + 16 * lane);
+    ml[0] = st.m[0];
+    ml[1] = lsum[0];
+    ml[2] = st.m[1];
+    ml[3] = lsum[1];
   }
   __syncthreads();
-  float m = -__builtin_inff();
 #pragma unroll
-  for (int g = 0; g < KG; ++g)
-    m = fmaxf(m, *(const float*)(slot(g * SP::NRG + rg, g * KEEP) + 8 * li));
-  float f[KG], l = 0.f;
+  for (int qt = 0; qt < 2; ++qt) {
+    float mg[KG], f[KG], m = -__builtin_inff(), l = 0.f;
 #pragma unroll
-  for (int g = 0; g < KG; ++g) {
-    const float* const ml = (const float*)(slot(g * SP::NRG + rg, g * KEEP) + 8 * li);
-    f[g] = ml[0] == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(ml[0] - m);
-    l += ml[1] * f[g];
-  }
-  const float inv = l > 0.f ? 1.f / l : 0.f;
+    for (int g = 0; g < KG; ++g) {
+      mg[g] = *(const float*)(slot(g * SP::NRG + rg, g * KEEP) + 16 * (lane % 16) + 8 * qt);
+      m = fmaxf(m, mg[g]);
+    }
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt) {
-    if (dt / KEEP != kg) continue;
+    for (int g = 0; g < KG; ++g) {
+      f[g] = mg[g] == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(mg[g] - m);
+      l += f[g] *
+           *(const float*)(slot(g * SP::NRG + rg, g * KEEP) + 16 * (lane % 16) + 8 * qt + 4);
+    }
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    const bool ok = qrow + 16 * qt < N;
+    __bf16* const orow = oh + (int64_t)(qrow + 16 * qt) * o_st + 4 * (lane / 16);
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
+    for (int dt = 0; dt < 8; ++dt) {
+      if (dt / KEEP != kg) continue;
       f32x4 acc = f32x4{};
 #pragma unroll
       for (int g = 0; g < KG; ++g) {
-        const f32x4 part =
-            g == kg ? f32x4{st.o[dt][4 * a], st.o[dt][4 * a + 1], st.o[dt][4 * a + 2],
-                            st.o[dt][4 * a + 3]}
-                    : *(const f32x4*)(slot(g * SP::NRG + rg, dt) + 1024 * a + 16 * lane);
+        const f32x4 part = g == kg ? st.o[dt][qt]
+                                   : *(const f32x4*)(slot(g * SP::NRG + rg, dt) + 1024 * qt +
+                                                     16 * lane);
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[b] += part[b] * f[g];
       }
-      typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
       bf16x4 w;
 #pragma unroll
       for (int b = 0; b < 4; ++b) w[b] = (__bf16)(acc[b] * inv);
-      if (row_ok) *(bf16x4*)(orow + 32 * dt + 8 * a + 4 * hl) = w;
+      if (ok) *(bf16x4*)(orow + 16 * dt) = w;
     }
   }
 }
@@ -690,7 +751,7 @@ __device__ __forceinline__ void attn_tile(
     const uint32_t* __restrict__ rows, int32_t P, float scale_log2) {
   using TL = Tile;
   using SP = Split<KG>;
-  constexpr int KTW = SP::KTW;
+  constexpr int NU = SP::NU;
   constexpr bool SPARSE = MODE != ATTN_DENSE;
   constexpr bool EXACT = MODE == ATTN_EXACT;
   constexpr bool PAIR = SP::ROWS > BLOCK;        // two query blocks, else (part of) one
@@ -702,8 +763,8 @@ __device__ __forceinline__ void attn_tile(
   const int tid = threadIdx.x;
   const int wave = tid / 64;
   const int lane = tid % 64;
-  const int hl = lane / 32;
-  const int li = lane % 32;
+  const int g16 = lane / 16;
+  const int li = lane % 16;
 
   const int rg = wave % SP::NRG, kg = wave / SP::NRG;
   const bool upper = wave >= TL::NW / 2;        // follows half a step behind
@@ -735,13 +796,16 @@ __device__ __forceinline__ void attn_tile(
   };
   const FragAddr fa = frag_addr(lane, KG == 1 ? 0 : kg * SP::NK);
 
-  // Q fragments: row qrow, k-slots d = 16*stp + 8*hl + 0..7.
+  // Q fragments: rows qrow and qrow + 16, k-slots d = 32*stp + 8*g16 + 0..7.
   const int qrow = wrow + li;
-  bf16x8 qf[8];
+  bf16x8 qf[4][2];
 #pragma unroll
-  for (int stp = 0; stp < 8; ++stp)
-    qf[stp] = qrow < N ? *(const bf16x8*)(qh + (int64_t)qrow * q_st + 16 * stp + 8 * hl)
-                       : bf16x8{};
+  for (int stp = 0; stp < 4; ++stp)
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt)
+      qf[stp][qt] = qrow + 16 * qt < N ? *(const bf16x8*)(qh + (int64_t)(qrow + 16 * qt) * q_st +
+                                                          32 * stp + 8 * g16)
+                                       : bf16x8{};
 
   // Exact mode: the first of the wave's 32 rows that lies in the query
   // block's second frame (the first frame holds the block's first qfirst
@@ -754,15 +818,15 @@ __device__ __forceinline__ void attn_tile(
   // Masks the scores of the key block of step word w for this wave's query
   // block: a key block that block does not keep has no valid keys.
   // `second`: the wave holds rows of query block 2p + 1.
-  auto mask_block = [&](Scores<KTW>& sc, uint32_t w, bool second) {
+  auto mask_block = [&](Scores<NU>& sc, uint32_t w, bool second) {
     const int kb = kb_of(w);
     const uint32_t kept_bit = second ? 31u : 30u;      // block form
     const uint32_t pat_shift = second ? 28u : 24u;     // exact form
     if constexpr (EXACT)
-      mask_exact<BLOCK, KTW>(sc, (w >> pat_shift) & 0xFu, (int)((w >> 16) & 0xFFu),
+      mask_exact<BLOCK, NU>(sc, (w >> pat_shift) & 0xFu, (int)((w >> 16) & 0xFFu),
                              N - kb * BLOCK, sec_from, koff);
     else
-      mask_tail<KTW>(sc, lane, ((w >> kept_bit) & 1u) ? N - kb * BLOCK - koff : 0);
+      mask_tail<NU>(sc, lane, ((w >> kept_bit) & 1u) ? N - kb * BLOCK - koff : 0);
   };
 
   // The walk (sparse modes) or the key blocks nb-1 .. 0 (dense): n steps.
@@ -819,22 +883,19 @@ __device__ __forceinline__ void attn_tile(
 
   WaveState ws;
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt) ws.o[dt] = f32x16{};
-  ws.m = -__builtin_inff();
-  ws.l = f32x4{};
-  ws.l0 = 0.f;
-  ws.l1 = 0.f;
-  constexpr int RSUM = MODE == ATTN_BLOCK || KG > 1 ? RSUM_VALU : RSUM_MFMA;
-  // A operand of the row-sum MFMA (16x16x32): read as P^T's B operand, lane
-  // group g = lane/16 of the 32x32 P register holds q rows 16*(g%2) + 0..15,
-  // so A row 0 takes groups 0 and 2 (rows 0-15) and row 1 groups 1 and 3.
-  bf16x8 ones;
-  {
-    const int ai = lane % 16, ag = lane / 16;
-    const bool one = (ai == 0 && ag % 2 == 0) || (ai == 1 && ag % 2 == 1);
+  for (int qt = 0; qt < 2; ++qt) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) ones[e] = one ? (__bf16)1.f : (__bf16)0.f;
+    for (int dt = 0; dt < 8; ++dt) ws.o[dt][qt] = f32x4{};
+    ws.m[qt] = -__builtin_inff();
+    ws.lt[qt] = f32x4{};
+    ws.l[qt] = 0.f;
   }
+  constexpr int RSUM = MODE == ATTN_BLOCK || KG > 1 ? RSUM_VALU : RSUM_MFMA;
+  // A operand of the row-sum MFMA: rows 0, 4, 8 and 12 (register 0 of every
+  // lane of the result) take all 32 keys, the others none.
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = lane % 4 == 0 ? (__bf16)1.f : (__bf16)0.f;
 
   if (n > 0) {
     // LDS stages: K(b) in K slot b % 2, V(b) in V slot b % 2.
@@ -860,11 +921,11 @@ __device__ __forceinline__ void attn_tile(
     issue_tile(v_slot0, rv_at(w0), vp);
     issue_tile(k_slot0 + TL::BYTES, rk_at(w1), kp);
     wait_loads_and_sync();
-    Scores<KTW> sc;
-    compute_scores<KTW>(k_lds, qf, sc, fa);   // S(0)
+    Scores<NU> sc;
+    compute_scores<NU>(k_lds, qf, sc, fa);   // S(0)
     mask_block(sc, w0, second(upper));
-    Probs<KTW> pr;
-    if (lead) softmax_phase<KTW, RSUM>(sc, ws, pr, scale_log2, nullptr);   // P(0)
+    Probs<NU> pr;
+    if (lead) softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, nullptr);   // P(0)
     __syncthreads();
     for (int j = 0; j < n; ++j) {
       // Word of step j+3 from the walk's LDS, read now and used at the end of
@@ -880,17 +941,17 @@ __device__ __forceinline__ void attn_tile(
       const char* const vj = v_lds + (j & 1) * TL::BYTES;          // V(j)
       // half-period 2j
       if (lead) {
-        gemm_phase<KTW, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones, &sl);
+        gemm_phase<NU, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones, &sl);
         mask_block(sc, w1, second(false));
       } else {
-        softmax_phase<KTW, RSUM>(sc, ws, pr, scale_log2, &sl);
+        softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, &sl);
       }
       __syncthreads();
       // half-period 2j+1
       if (lead) {
-        if (j + 1 < n) softmax_phase<KTW, RSUM>(sc, ws, pr, scale_log2, nullptr);
+        if (j + 1 < n) softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, nullptr);
       } else {
-        gemm_phase<KTW, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones, nullptr);
+        gemm_phase<NU, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones, nullptr);
         mask_block(sc, w1, second(true));
       }
       wait_loads_and_sync();
@@ -901,32 +962,36 @@ __device__ __forceinline__ void attn_tile(
     __syncthreads();
   }
 
-  // Row sums: the l tile holds row c in register 0 of lane c and row c + 16 in
-  // register 1 (c < 16); the VALU form's halves are in lanes l and l^32.
-  float lsum;
-  if constexpr (RSUM == RSUM_MFMA) {
-    const float r0s = __shfl(ws.l[0], li), r1s = __shfl(ws.l[1], li & 15);
-    lsum = li < 16 ? r0s : r1s;
-  } else {
-    const float lpart = ws.l0 + ws.l1;
-    lsum = lpart + __shfl_xor(lpart, 32);
+  // Row sums: whole in every lane (RSUM_MFMA), or a part in each of a row's
+  // four lanes.
+  float lsum[2];
+#pragma unroll
+  for (int qt = 0; qt < 2; ++qt) {
+    if constexpr (RSUM == RSUM_MFMA) {
+      lsum[qt] = ws.lt[qt][0];
+    } else {
+      const float l2 = ws.l[qt] + __shfl_xor(ws.l[qt], 16);
+      lsum[qt] = l2 + __shfl_xor(l2, 32);
+    }
   }
-  __bf16* const orow = oh + (int64_t)qrow * o_st;
   if constexpr (KG > 1) {
-    combine_groups<KG>(lds, ws, lsum, orow, qrow < N, wave, lane);
-  } else if (qrow < N) {
+    combine_groups<KG>(lds, ws, lsum, oh, o_st, qrow, N, wave, lane);
+  } else {
     // Every wave holds whole rows: O / l, rounded to bf16.
-    const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int qt = 0; qt < 2; ++qt) {
+      const float inv = lsum[qt] > 0.f ? 1.f / lsum[qt] : 0.f;
+      __bf16* const orow = oh + (int64_t)(qrow + 16 * qt) * o_st + 4 * g16;
+      if (qrow + 16 * qt < N) {
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-        bf16x4 w;
+        for (int dt = 0; dt < 8; ++dt) {
+          bf16x4 w;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) w[b] = (__bf16)(ws.o[dt][4 * a + b] * inv);
-        *(bf16x4*)(orow + 32 * dt + 8 * a + 4 * hl) = w;
+          for (int b = 0; b < 4; ++b) w[b] = (__bf16)(ws.o[dt][qt][b] * inv);
+          *(bf16x4*)(orow + 16 * dt) = w;
+        }
       }
+    }
   }
 }
 
