@@ -82,7 +82,7 @@ typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int D = 128;             // head_dim
-constexpr float RESCALE_SLACK = 8.f;
+constexpr float HEADROOM = 7.f;
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
@@ -310,9 +310,10 @@ enum RowSums { RSUM_MFMA = 0, RSUM_VALU = 1 };
 
 struct WaveState {
   f32x4 o[8][2];   // O^T tiles [d tile][query tile]: d = 16*dt + C row
-  float m[2];      // running max (log2 domain), the same in a row's four lanes
+  float m[2];      // reference of the exponentials (log2 domain), the same in a row's four lanes
   f32x4 lt[2];     // RSUM_MFMA: row sums
   float l[2];      // RSUM_VALU: partial row sums of the lane's keys
+  int ready;       // every row has a finite m
 };
 
 // Keys at or past N (ragged last block) do not exist: their scores become
@@ -383,23 +384,11 @@ struct Probs {
   bf16x8 p[NU][2];   // [32-key group][query tile]
 };
 
-// Softmax phase of the ping-pong schedule: block j's scores (in `sc`) become
-// its probabilities P (bf16, in `pr`), with the running max and, when the
-// max is raised, the rescale of O and l done here so that the next GEMM phase
-// only multiplies (with RSUM_VALU, P is also added into l here; with
-// RSUM_MFMA the GEMM phase does it).  `sl` (may be null) carries tile
-// loads to issue along the way.  Scheduling barriers every 8 scores keep the
-// compiler from hoisting many exponentials at once (S, P, O and Q already
-// fill the register file).
+// Raises the reference m of every row whose largest score of the step lies
+// above it, to HEADROOM above that score, and rescales the row's O and l.
 template <int NU, int RSUM>
-__device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& st,
-                                              Probs<NU>& pr, float scale_log2,
-                                              const StepLoads* sl) {
-  constexpr int NLOADS = 2 * Tile::LOADS;
-  constexpr int GROUPS = 4 * NU;                     // pairs of tiles of 4 scores
-  constexpr int PER = (NLOADS + GROUPS - 1) / GROUPS;
-  constexpr int EVERY = GROUPS > NLOADS ? GROUPS / NLOADS : 1;
-  int issued = 0;
+__device__ __forceinline__ void raise_max(const Scores<NU>& sc, WaveState& st,
+                                          float scale_log2) {
   float mx[2];
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt) {
@@ -410,23 +399,37 @@ __device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& s
       for (int r = 0; r < 4; ++r) mx[qt] = fmaxf(mx[qt], sc.s[kt][qt][r]);
   }
   row_max(mx[0], mx[1]);
-  const float m0 = mx[0] * scale_log2, m1 = mx[1] * scale_log2;
-  const bool raise0 = m0 > st.m[0] + RESCALE_SLACK, raise1 = m1 > st.m[1] + RESCALE_SLACK;
-  if (__builtin_amdgcn_ballot_w64(raise0 || raise1)) {
-    const float a[2] = {raise0 ? __builtin_amdgcn_exp2f(st.m[0] - m0) : 1.f,
-                        raise1 ? __builtin_amdgcn_exp2f(st.m[1] - m1) : 1.f};
-    st.m[0] = raise0 ? m0 : st.m[0];
-    st.m[1] = raise1 ? m1 : st.m[1];
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt) {
-      if constexpr (RSUM == RSUM_MFMA) st.lt[qt][0] *= a[qt];
-      else st.l[qt] *= a[qt];
+  for (int qt = 0; qt < 2; ++qt) {
+    const float top = mx[qt] * scale_log2;
+    const bool raise = top > st.m[qt];
+    const float m = raise ? top + HEADROOM : st.m[qt];
+    const float a = raise ? __builtin_amdgcn_exp2f(st.m[qt] - m) : 1.f;
+    st.m[qt] = m;
+    if constexpr (RSUM == RSUM_MFMA) st.lt[qt][0] *= a;
+    else st.l[qt] *= a;
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) st.o[dt][qt] *= a[qt];
-    }
+    for (int dt = 0; dt < 8; ++dt) st.o[dt][qt] *= a;
   }
-  const float msub[2] = {st.m[0] == -__builtin_inff() ? 0.f : st.m[0],
-                         st.m[1] == -__builtin_inff() ? 0.f : st.m[1]};
+  st.ready = __builtin_amdgcn_ballot_w64(st.m[0] == -__builtin_inff() ||
+                                         st.m[1] == -__builtin_inff()) == 0;
+}
+
+// P = 2^(s*scale - m) in bf16 from one step's scores, l += its row sums
+// (RSUM_VALU), with the tile loads in `sl` (may be null) issued along the way.
+// Returns the bits of all probabilities or-ed together.  Scheduling barriers
+// every 8 scores keep the compiler from hoisting many exponentials at once
+// (S, P, O and Q already fill the register file).
+template <int NU, int RSUM>
+__device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU>& pr,
+                                                  float (&l)[2], const float (&m)[2],
+                                                  float scale_log2, const StepLoads* sl) {
+  constexpr int NLOADS = 2 * Tile::LOADS;
+  constexpr int GROUPS = 4 * NU;                     // groups of 4 scores
+  constexpr int PER = (NLOADS + GROUPS - 1) / GROUPS;
+  constexpr int EVERY = GROUPS > NLOADS ? GROUPS / NLOADS : 1;
+  int issued = 0;
+  uint32_t bits = 0u;
 #pragma unroll
   for (int u = 0; u < NU; ++u)
 #pragma unroll
@@ -440,36 +443,68 @@ __device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& s
 #pragma unroll
         for (int r = 0; r < 4; r += 2) {
           const float a = __builtin_amdgcn_exp2f(
-              __builtin_fmaf(sc.s[2 * u + t][qt][r], scale_log2, -msub[qt]));
+              __builtin_fmaf(sc.s[2 * u + t][qt][r], scale_log2, -m[qt]));
           const float b = __builtin_amdgcn_exp2f(
-              __builtin_fmaf(sc.s[2 * u + t][qt][r + 1], scale_log2, -msub[qt]));
-          if constexpr (RSUM == RSUM_VALU) st.l[qt] += a + b;
+              __builtin_fmaf(sc.s[2 * u + t][qt][r + 1], scale_log2, -m[qt]));
+          if constexpr (RSUM == RSUM_VALU) l[qt] += a + b;
           const bf16x2 pk = {(__bf16)a, (__bf16)b};
+          bits |= __builtin_bit_cast(uint32_t, pk);
           pr.p[u][qt][4 * t + r] = pk[0];
           pr.p[u][qt][4 * t + r + 1] = pk[1];
         }
       }
   if (sl)
     for (; issued < NLOADS; ++issued) issue_step_load(*sl, issued);
+  return bits;
+}
+
+// Softmax phase of the ping-pong schedule: block j's scores (in `sc`) become
+// its probabilities P (bf16, in `pr`), against the rows' reference m as it
+// stands.  m is HEADROOM above the largest score it was set from, so p stays
+// far below 2 until a score exceeds that one by HEADROOM + 1; then some p
+// (rounded to bf16) is at least 2, which sets the top exponent bit of its half
+// of the word (inf and NaN do too), and the wave raises m and does the step's
+// probabilities again.  So a step usually takes no row maximum: one or3 per
+// four scores instead of one max3 per two and the exchange between a row's
+// lanes.  The result is exact either way because O and l always use the same
+// m.  Until every row has an m (st.ready), m is raised first.
+template <int NU, int RSUM>
+__device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& st,
+                                              Probs<NU>& pr, float scale_log2,
+                                              const StepLoads* sl) {
+  const bool first = !__builtin_amdgcn_readfirstlane(st.ready);
+  if (first) raise_max<NU, RSUM>(sc, st, scale_log2);
+  float l[2] = {st.l[0], st.l[1]};
+  float m[2];
+#pragma unroll
+  for (int qt = 0; qt < 2; ++qt) m[qt] = st.m[qt] == -__builtin_inff() ? 0.f : st.m[qt];
+  const uint32_t bits = probabilities<NU, RSUM>(sc, pr, l, m, scale_log2, sl);
+  if (__builtin_amdgcn_ballot_w64((bits & 0x40004000u) != 0u) && !first) {
+    raise_max<NU, RSUM>(sc, st, scale_log2);
+    l[0] = st.l[0];
+    l[1] = st.l[1];
+    m[0] = st.m[0];
+    m[1] = st.m[1];
+    probabilities<NU, RSUM>(sc, pr, l, m, scale_log2, nullptr);
+  }
+  st.l[0] = l[0];
+  st.l[1] = l[1];
 }
 
 // GEMM phase of the ping-pong schedule: with RSUM_MFMA, l += the row sums of
 // P(j) (one MFMA per 32 keys and query tile, `ones` its A operand); then
 // O += P(j) V(j) and S(j+1) = K(j+1) Q^T into `sc`, with K and V fragments
-// read AHEAD fragments early and the tile loads in `sl` (may be null) spread
-// over the phase.  The row-sum MFMAs come first: their operands are already in
+// read AHEAD fragments early.  The row-sum MFMAs come first: their operands are already in
 // registers, so they run while the first fragments arrive from LDS.
 template <int NU, int RSUM>
 __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
                                            const bf16x8 (&qf)[4][2], Scores<NU>& sc,
                                            const Probs<NU>& pr, WaveState& st,
-                                           const FragAddr& fa, const bf16x8& ones,
-                                           const StepLoads* sl) {
+                                           const FragAddr& fa, const bf16x8& ones) {
   constexpr int NS = 8 * NU;   // K fragments: (key tile, d-step)
   constexpr int NP = 8 * NU;   // V fragments: (d tile, 32-key group)
   constexpr int NF = NS + NP;
-  constexpr int AHEAD = 6;
-  constexpr int NLOADS = 2 * Tile::LOADS;
+  constexpr int AHEAD = NU == 4 ? 8 : 4;
   // Fragment i < NP: V^T, d tile i/NU, key group i%NU.  Fragment NP + f: K, key
   // tile f/4, d-step f%4.  P(j) (with its row sums) is done before S(j+1) is
   // produced, so the two are never live together.
@@ -491,8 +526,8 @@ __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
         __builtin_amdgcn_sched_barrier(0);
       }
   }
-  // What MFMA m of the phase's 2 * NF carries along: a fragment read at every
-  // second one, the tile loads evenly spread.
+  // What MFMA m of the phase's 2 * NF carries along: the read of half a V
+  // fragment, or of a K fragment at every second one.
   i16x4 lo = i16x4{};
   auto carry = [&](int m) {
     const int i = m / 2 + AHEAD;
@@ -505,7 +540,6 @@ __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
         fr[i] = join(lo, v_half(lds_v, fa, i / NU, i % NU, 1));
       }
     }
-    if (sl && m % (2 * NF / NLOADS) == 0) issue_step_load(*sl, m / (2 * NF / NLOADS));
   };
   // The fragments of one accumulator pair (NU for a d tile, 4 for a key tile)
   // one after the other into the first query tile's accumulator, then in the
@@ -890,7 +924,8 @@ __device__ __forceinline__ void attn_tile(
     ws.lt[qt] = f32x4{};
     ws.l[qt] = 0.f;
   }
-  constexpr int RSUM = MODE == ATTN_BLOCK || KG > 1 ? RSUM_VALU : RSUM_MFMA;
+  ws.ready = 0;
+  constexpr int RSUM = KG > 1 ? RSUM_VALU : RSUM_MFMA;
   // A operand of the row-sum MFMA: rows 0, 4, 8 and 12 (register 0 of every
   // lane of the result) take all 32 keys, the others none.
   bf16x8 ones;
@@ -941,7 +976,7 @@ __device__ __forceinline__ void attn_tile(
       const char* const vj = v_lds + (j & 1) * TL::BYTES;          // V(j)
       // half-period 2j
       if (lead) {
-        gemm_phase<NU, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones, &sl);
+        gemm_phase<NU, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones);
         mask_block(sc, w1, second(false));
       } else {
         softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, &sl);
@@ -949,9 +984,9 @@ __device__ __forceinline__ void attn_tile(
       __syncthreads();
       // half-period 2j+1
       if (lead) {
-        if (j + 1 < n) softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, nullptr);
+        if (j + 1 < n) softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, &sl);
       } else {
-        gemm_phase<NU, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones, nullptr);
+        gemm_phase<NU, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones);
         mask_block(sc, w1, second(true));
       }
       wait_loads_and_sync();
