@@ -205,7 +205,7 @@ typedef struct lvsa_block_mask {
 /* Device view of an uploaded handle.  Errors: EINVAL if never uploaded. */
 lvsa_status lvsa_csr_device_view(const lvsa_csr* csr, lvsa_block_mask* out);
 
-/* Device builder: the same CSR computed on the GPU (three short kernels on
+/* Device builder: the same CSR computed on the GPU (one short kernel on
  * `stream`), written to caller-owned device buffers (no host round trip, no
  * allocation, no memset).
  *   d_row_ptr     device int32[nb + 1]

@@ -66,11 +66,6 @@ __host__ __device__ inline int32_t anchors_below(const FrameCfg& c, int32_t f) {
   return period_anchors_below(c, f) + e - period_anchors_below(c, e);
 }
 
-// Frames of [lo, hi] that are not anchors.
-__host__ __device__ inline int32_t free_frames(const FrameCfg& c, int32_t lo, int32_t hi) {
-  return (hi - lo + 1) - (anchors_below(c, hi + 1) - anchors_below(c, lo));
-}
-
 // Expanded window (Alg. 1).  Alg. 1 widens the adaptive window [l, h] one
 // frame at a time on the side with more room (room below a = l, above
 // b = T-1-h; equal room goes to the low side, or to the high side under
@@ -103,9 +98,12 @@ __host__ __device__ inline void grown_window(int32_t l, int32_t h, int32_t a, in
 //   BASIC    Def. 2
 //   ADAPTIVE shifted to keep 2W+1 frames (Sec. 2, "Overlapping frames")
 //   EXPANDED Alg. 1, as above
-// Returns the number of Alg. 1 growth steps (0 for the other rules).
+// `below(f)` is anchors_below(c, f), by whatever means the caller has it (the
+// closed form, or a table of it).  Returns the number of Alg. 1 growth steps
+// (0 for the other rules).
+template <typename Below>
 __host__ __device__ inline int32_t frame_window(const FrameCfg& c, int32_t t,
-                                                int32_t* lo_out,
+                                                const Below& below, int32_t* lo_out,
                                                 int32_t* hi_out) {
   const int32_t T = c.T, W = c.W;
   if (c.mode == LVSA_WINDOW_BASIC) {
@@ -124,7 +122,8 @@ __host__ __device__ inline int32_t frame_window(const FrameCfg& c, int32_t t,
       const int32_t g = (g_lo + g_hi) / 2;
       int32_t lo, hi;
       grown_window(l, h, a, b, g, c.tie_high != 0, &lo, &hi);
-      if (free_frames(c, lo, hi) >= target)
+      // Frames of [lo, hi] that are not anchors.
+      if ((hi - lo + 1) - (below(hi + 1) - below(lo)) >= target)
         g_hi = g;
       else
         g_lo = g + 1;
@@ -135,16 +134,21 @@ __host__ __device__ inline int32_t frame_window(const FrameCfg& c, int32_t t,
   return steps;
 }
 
+__host__ __device__ inline int32_t frame_window(const FrameCfg& c, int32_t t,
+                                                int32_t* lo_out, int32_t* hi_out) {
+  return frame_window(c, t, [&](int32_t f) { return anchors_below(c, f); }, lo_out, hi_out);
+}
+
 // First and last segment touched by block b (tokens b*B .. min((b+1)*B, N)-1):
 // frames 0..T-1 for video tokens, segment T for the text tokens after them.
 __host__ __device__ inline void block_frame_range(int32_t b, int32_t T,
                                                   int32_t P, int32_t B,
                                                   int32_t N, int32_t* first,
                                                   int32_t* last) {
-  const int64_t t0 = (int64_t)b * B;
-  const int64_t end = t0 + B < (int64_t)N ? t0 + B : (int64_t)N;
-  *first = (int32_t)(t0 / P < T ? t0 / P : T);
-  *last = (int32_t)((end - 1) / P < T ? (end - 1) / P : T);
+  const int32_t t0 = b * B;   // N + B fits in int32
+  const int32_t end = imin(t0 + B, N);
+  *first = imin(t0 / P, T);
+  *last = imin((end - 1) / P, T);
 }
 
 // Key blocks of segment tau: frame tau's tokens tau*P .. tau*P+P-1, or the

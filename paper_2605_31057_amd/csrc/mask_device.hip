@@ -5,208 +5,183 @@
 // without a host round trip, so a denoising loop can rebuild the mask for
 // step s on the stream that then runs attention.
 //
-// Three launches on the stream, each workgroup of the first and the last
-// handling a pair of query blocks 2p and 2p+1 (the last pair of an odd nb has
-// one), whose frames overlap, so the windows are computed once for both:
-//   1. one workgroup per pair: the windows of the pair's frames (Alg. 1) into
-//      LDS, then every key block tested in parallel against both query
-//      blocks; the two row lengths go to row_ptr[qb + 1];
-//   2. one workgroup: an in-place inclusive scan of row_ptr;
-//   3. one workgroup per pair: the same tests again, kept key blocks
-//      compacted in ascending order (wave ballots and a per-chunk prefix) and
-//      written as block indices and/or token-exact entry words.
-// Every thread tests its own candidates with closed-form rules, so a row
-// costs a few passes over nb candidates whatever its length.
+// One launch.  What a row keeps has a closed form: the windows of a query
+// block's frames each contain their own frame, so together they are one run of
+// frames and its blocks one run [b0, b1] of key blocks; outside that run a key
+// block is kept iff it touches an anchor frame or the text, the same for every
+// row.  So every workgroup makes
+//   - a table of the anchors below each frame and the windows of all frames
+//     (Alg. 1, one frame per thread, the binary search on that table);
+//   - a bitmap of the key blocks that touch an anchor or the text, and the
+//     count of such blocks before each of its words,
+// from which a row's length and the place of a kept block in its row are a few
+// LDS reads.  Its rows start where the lengths of all rows before them add up
+// to, which it sums itself; then it writes its rows, every thread its own key
+// blocks.  The tables are small (a frame and a few key blocks per thread), so
+// making them again in every workgroup costs less than a launch that would
+// make them once: what bounds the builder is latency.  Wan 6x (1,475 blocks,
+// 121 frames), block form then token-exact form: 167 us with three launches each
+// (row lengths, scan, rows; every key block tested against every row, twice),
+// 31 us now.
 #include "internal.h"
 
 namespace lvsa {
 namespace {
 
-constexpr int kRowThreads = 256;
-constexpr int kRowWaves = kRowThreads / 64;
-constexpr int kScanThreads = 1024;
+constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / 64;
 
-// Query frames one workgroup can hold (a query-block pair touches at most
-// 2B/P + 2 frames; checked before launch).
+// Frames that a query-block pair may touch (checked before launch).
 constexpr int kMaxRowFrames = 1024;
 
-struct RowFrames {
-  int32_t f0, f1;                  // segments touched by the pair's query blocks
-  int16_t lo[kMaxRowFrames];       // window of frame f0 + i
-  int16_t hi[kMaxRowFrames];
+// Key blocks: nb * nb fits in int32.
+constexpr int kMaxBlocks = 46340;
+constexpr int kMaxWords = (kMaxBlocks + 63) / 64;
+
+// Rows per workgroup at most, and the number of workgroups aimed at (two per
+// CU).
+constexpr int kMaxRows = 128;
+constexpr int kGroups = 512;
+static_assert((kMaxBlocks + kGroups - 1) / kGroups <= kMaxRows, "rows per workgroup");
+
+struct Tables {
+  int16_t below[LVSA_MAX_FRAMES + 1];   // anchors among frames 0..f-1
+  int16_t lo[LVSA_MAX_FRAMES];          // window of frame t
+  int16_t hi[LVSA_MAX_FRAMES];
+  uint64_t common[kMaxWords + 1];       // key blocks every row keeps
+  int32_t rank[kMaxWords + 1];          // common blocks before word w
 };
 
-// tau in A(t) for segments t, tau (segment T = the text tokens, attended by
-// and attending to everything).
-__device__ inline bool seg_attends(const FrameCfg& c, const RowFrames& rf, int32_t t,
-                                   int32_t tau) {
-  if (t == c.T || tau == c.T) return true;
-  if (is_anchor(c, tau)) return true;
-  const int32_t i = t - rf.f0;
-  return rf.lo[i] <= tau && tau <= rf.hi[i];
-}
-
-// Windows of the frames touched by query blocks qb0..qb1 into LDS.
-__device__ inline void load_row_frames(const FrameCfg& c, int32_t qb0, int32_t qb1,
-                                       int32_t P, int32_t B, int32_t N, RowFrames* rf) {
-  if (threadIdx.x == 0) {
-    int32_t a, b;
-    block_frame_range(qb0, c.T, P, B, N, &rf->f0, &a);
-    block_frame_range(qb1, c.T, P, B, N, &b, &rf->f1);
-  }
-  __syncthreads();
-  const int32_t last = imin(rf->f1, c.T - 1);
-  for (int32_t t = rf->f0 + (int32_t)threadIdx.x; t <= last; t += kRowThreads) {
-    int32_t lo, hi;
-    frame_window(c, t, &lo, &hi);
-    rf->lo[t - rf->f0] = (int16_t)lo;
-    rf->hi[t - rf->f0] = (int16_t)hi;
-  }
-  __syncthreads();
-}
-
-// Whether a query block touching segments t0..t1 keeps key block kb.
-__device__ inline bool keeps(const FrameCfg& c, const RowFrames& rf, int32_t t0,
-                             int32_t t1, int32_t kb, int32_t P, int32_t B, int32_t N) {
-  int32_t g0, g1;
-  block_frame_range(kb, c.T, P, B, N, &g0, &g1);
-  for (int32_t t = t0; t <= t1; ++t)
-    for (int32_t tau = g0; tau <= g1; ++tau)
-      if (seg_attends(c, rf, t, tau)) return true;
-  return false;
-}
-
-// Per-pair test: which of the pair's query blocks keep key block kb.
-struct RowTest {
-  int32_t qb0, qb1;          // 2p and 2p+1 (equal for the last pair of an odd nb)
-  int32_t a0, a1, b0, b1;    // segments touched by qb0 and by qb1
+// One row: query segments f0..f1, the run of key blocks of their windows and
+// the common blocks before it and up to its end, where the row starts.
+struct Row {
+  int32_t f0, f1, b0, b1, r0, r1, len;
 };
 
-__device__ inline RowTest row_test(const FrameCfg& c, int32_t p, int32_t P, int32_t B,
-                                   int32_t N, int32_t nb) {
-  RowTest rt;
-  rt.qb0 = 2 * p;
-  rt.qb1 = imin(2 * p + 1, nb - 1);
-  block_frame_range(rt.qb0, c.T, P, B, N, &rt.a0, &rt.a1);
-  block_frame_range(rt.qb1, c.T, P, B, N, &rt.b0, &rt.b1);
-  return rt;
+// Common key blocks below b (0 <= b <= nb).
+__device__ inline int32_t common_below(const Tables& tb, int32_t b) {
+  const uint64_t w = tb.common[b / 64] & ((1ull << (b % 64)) - 1ull);
+  return tb.rank[b / 64] + (int32_t)__popcll(w);
 }
 
-__device__ inline void kept_by(const FrameCfg& c, const RowFrames& rf, const RowTest& rt,
-                               int32_t kb, int32_t P, int32_t B, int32_t N, bool* k0,
-                               bool* k1) {
-  *k0 = keeps(c, rf, rt.a0, rt.a1, kb, P, B, N);
-  *k1 = rt.qb1 != rt.qb0 && keeps(c, rf, rt.b0, rt.b1, kb, P, B, N);
-}
-
-// Sums of two per-thread counts over the workgroup (thread 0's result).
-__device__ inline void block_sum2(int32_t (&v)[2], int32_t (*s_cnt)[kRowWaves]) {
-  for (int i = 0; i < 2; ++i) {
-    for (int off = 32; off > 0; off >>= 1) v[i] += __shfl_xor(v[i], off);
-    if (threadIdx.x % 64 == 0) s_cnt[i][threadIdx.x / 64] = v[i];
-  }
-  __syncthreads();
-  if (threadIdx.x == 0)
-    for (int i = 0; i < 2; ++i) {
-      v[i] = 0;
-      for (int w = 0; w < kRowWaves; ++w) v[i] += s_cnt[i][w];
+__device__ inline Row make_row(const Tables& tb, const FrameCfg& c, int32_t qb, int32_t P,
+                               int32_t B, int32_t N, int32_t nb) {
+  Row r;
+  block_frame_range(qb, c.T, P, B, N, &r.f0, &r.f1);
+  if (r.f1 == c.T) {   // text queries keep every block
+    r.b0 = 0;
+    r.b1 = nb - 1;
+  } else {
+    int32_t lo = tb.lo[r.f0], hi = tb.hi[r.f0];
+    for (int32_t t = r.f0 + 1; t <= r.f1; ++t) {
+      lo = imin(lo, tb.lo[t]);
+      hi = imax(hi, tb.hi[t]);
     }
+    r.b0 = lo * P / B;
+    r.b1 = (hi * P + P - 1) / B;
+  }
+  r.r0 = common_below(tb, r.b0);
+  r.r1 = common_below(tb, r.b1 + 1);
+  r.len = (r.b1 - r.b0 + 1) + common_below(tb, nb) - (r.r1 - r.r0);
+  return r;
 }
 
-__global__ __launch_bounds__(kRowThreads) void count_rows_kernel(
-    FrameCfg c, int32_t P, int32_t B, int32_t* __restrict__ row_ptr) {
-  __shared__ RowFrames rf;
-  __shared__ int32_t s_cnt[2][kRowWaves];
-  const int32_t N = (int32_t)mask_tokens(c, P);
-  const int32_t nb = ceil_div(N, B);
-  const int32_t p = blockIdx.x;
-  const RowTest rt = row_test(c, p, P, B, N, nb);
-  load_row_frames(c, rt.qb0, rt.qb1, P, B, N, &rf);
-  int32_t cnt[2] = {0, 0};   // row qb0, row qb1
-  for (int32_t kb = threadIdx.x; kb < nb; kb += kRowThreads) {
-    bool k0, k1;
-    kept_by(c, rf, rt, kb, P, B, N, &k0, &k1);
-    cnt[0] += k0 ? 1 : 0;
-    cnt[1] += k1 ? 1 : 0;
-  }
-  block_sum2(cnt, s_cnt);
-  if (threadIdx.x == 0) {
-    row_ptr[rt.qb0 + 1] = cnt[0];
-    if (rt.qb1 != rt.qb0) row_ptr[rt.qb1 + 1] = cnt[1];
-    if (p == 0) row_ptr[0] = 0;
-  }
-}
-
-// In-place inclusive scan of row_ptr[1 .. rows] (chunks of kScanThreads).
-__global__ __launch_bounds__(kScanThreads) void scan_rows_kernel(int32_t rows,
-                                                                 int32_t* __restrict__ row_ptr) {
-  __shared__ int32_t s_scan[kScanThreads];
-  __shared__ int32_t s_carry;
-  const int32_t tid = threadIdx.x;
-  if (tid == 0) s_carry = 0;
+// Sum over the workgroup, in every thread (`s_sum`: one word per wave).
+__device__ inline int32_t block_sum(int32_t v, int32_t* s_sum) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  if (threadIdx.x % 64 == 0) s_sum[threadIdx.x / 64] = v;
   __syncthreads();
-  for (int32_t base = 0; base < rows; base += kScanThreads) {
-    const int32_t i = base + tid;
-    s_scan[tid] = i < rows ? row_ptr[i + 1] : 0;
-    __syncthreads();
-    for (int32_t off = 1; off < kScanThreads; off <<= 1) {
-      const int32_t y = tid >= off ? s_scan[tid - off] : 0;
-      __syncthreads();
-      s_scan[tid] += y;
-      __syncthreads();
-    }
-    if (i < rows) row_ptr[i + 1] = s_scan[tid] + s_carry;
-    __syncthreads();
-    if (tid == kScanThreads - 1) s_carry += s_scan[tid];
-    __syncthreads();
-  }
+  int32_t sum = 0;
+  for (int w = 0; w < kWaves; ++w) sum += s_sum[w];
+  return sum;
 }
 
-// The CSR rows of the pair's query blocks (col_idx and/or entry words,
-// either may be null).
-__global__ __launch_bounds__(kRowThreads) void fill_rows_kernel(
-    FrameCfg c, int32_t P, int32_t B, const int32_t* __restrict__ row_ptr,
+// Rows rows*g .. rows*g + rows - 1 of the mask (workgroup g); col_idx and
+// entry may be null.
+__global__ __launch_bounds__(kThreads) void build_rows_kernel(
+    FrameCfg c, int32_t P, int32_t B, int32_t rows, int32_t* __restrict__ row_ptr,
     int32_t* __restrict__ col_idx, uint32_t* __restrict__ entry) {
-  __shared__ RowFrames rf;
-  __shared__ int32_t s_wave[2][kRowWaves];
+  __shared__ Tables tb;
+  __shared__ Row row[kMaxRows];
+  __shared__ int32_t start[kMaxRows];
+  __shared__ int32_t s_sum[kWaves];
+  const int32_t tid = threadIdx.x, lane = tid % 64;
   const int32_t N = (int32_t)mask_tokens(c, P);
   const int32_t nb = ceil_div(N, B);
-  const int32_t p = blockIdx.x;
-  const RowTest rt = row_test(c, p, P, B, N, nb);
-  load_row_frames(c, rt.qb0, rt.qb1, P, B, N, &rf);
-  const int32_t lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-  int32_t pos[2] = {row_ptr[rt.qb0], row_ptr[rt.qb1]};
-  auto attends = [&](int32_t t, int32_t tau) { return seg_attends(c, rf, t, tau); };
-  for (int32_t base = 0; base < nb; base += kRowThreads) {
-    const int32_t kb = base + (int32_t)threadIdx.x;
-    bool k0 = false, k1 = false;
-    if (kb < nb) kept_by(c, rf, rt, kb, P, B, N, &k0, &k1);
-    const bool keep[2] = {k0, k1};
-    int32_t at[2];
-    for (int i = 0; i < 2; ++i) {
-      const uint64_t bal = __ballot(keep[i]);
-      at[i] = __popcll(bal & ((1ull << lane) - 1ull));
-      if (lane == 0) s_wave[i][wave] = __popcll(bal);
+  const int32_t first = rows * (int32_t)blockIdx.x;
+  const int32_t count = imin(rows, nb - first);
+
+  for (int32_t f = tid; f <= c.T; f += kThreads) tb.below[f] = (int16_t)anchors_below(c, f);
+  __syncthreads();
+  for (int32_t t = tid; t < c.T; t += kThreads) {
+    int32_t lo, hi;
+    frame_window(c, t, [&](int32_t f) { return (int32_t)tb.below[f]; }, &lo, &hi);
+    tb.lo[t] = (int16_t)lo;
+    tb.hi[t] = (int16_t)hi;
+  }
+  const int32_t words = nb / 64 + 1;   // bit nb is in the last word
+  for (int32_t base = 0; base < words * 64; base += kThreads) {
+    const int32_t kb = base + tid;
+    bool bit = false;
+    if (kb < nb) {
+      int32_t g0, g1;
+      block_frame_range(kb, c.T, P, B, N, &g0, &g1);
+      bit = g1 == c.T || tb.below[g1 + 1] > tb.below[g0];
     }
-    __syncthreads();
-    for (int i = 0; i < 2; ++i) {
-      int32_t off = 0, total = 0;
-      for (int w = 0; w < kRowWaves; ++w) {
-        off += w < wave ? s_wave[i][w] : 0;
-        total += s_wave[i][w];
+    const uint64_t bal = __ballot(bit);
+    if (lane == 0 && kb / 64 < words) tb.common[kb / 64] = bal;
+  }
+  __syncthreads();
+  if (tid < 64) {
+    int32_t carry = 0;
+    for (int32_t base = 0; base < words; base += 64) {
+      const int32_t v = base + lane < words ? (int32_t)__popcll(tb.common[base + lane]) : 0;
+      int32_t incl = v;
+      for (int off = 1; off < 64; off <<= 1) {
+        const int32_t y = __shfl_up(incl, off);
+        if (lane >= off) incl += y;
       }
-      at[i] += pos[i] + off;
-      pos[i] += total;
+      if (base + lane < words) tb.rank[base + lane] = carry + incl - v;
+      carry += __shfl(incl, 63);
     }
-    if (k0) {
-      if (col_idx) col_idx[at[0]] = kb;
-      if (entry) entry[at[0]] = exact_entry(kb, rt.a0, rt.a1, c.T, P, B, N, attends);
+  }
+  __syncthreads();
+
+  int32_t before = 0;
+  for (int32_t qb = tid; qb < first; qb += kThreads)
+    before += make_row(tb, c, qb, P, B, N, nb).len;
+  if (tid < count) row[tid] = make_row(tb, c, first + tid, P, B, N, nb);
+  before = block_sum(before, s_sum);   // its barrier also covers row[]
+  if (tid < count) {
+    int32_t at = before;
+    for (int32_t i = 0; i < tid; ++i) at += row[i].len;
+    start[tid] = at;
+    row_ptr[first + tid + 1] = at + row[tid].len;
+    if (first + tid == 0) row_ptr[0] = 0;
+  }
+  __syncthreads();
+
+  auto attends = [&](int32_t t, int32_t tau) {
+    return t == c.T || tau == c.T || tb.below[tau + 1] > tb.below[tau] ||
+           (tb.lo[t] <= tau && tau <= tb.hi[t]);
+  };
+  for (int32_t kb = tid; kb < nb; kb += kThreads) {
+    const bool common = (tb.common[kb / 64] >> (kb % 64)) & 1ull;
+    const int32_t rk = common_below(tb, kb);
+    int32_t g0 = 0, g1 = 0;
+    uint32_t kfirst = 0u;
+    if (entry) key_block_split(kb, c.T, P, B, N, &g0, &g1, &kfirst);
+    for (int32_t i = 0; i < count; ++i) {
+      const Row r = row[i];
+      const bool in_run = r.b0 <= kb && kb <= r.b1;
+      if (!common && !in_run) continue;
+      // Kept blocks of the row below kb.
+      const int32_t at = start[i] + (kb < r.b0 ? rk
+                                     : in_run  ? r.r0 + (kb - r.b0)
+                                               : rk + (r.b1 - r.b0 + 1) - (r.r1 - r.r0));
+      if (col_idx) col_idx[at] = kb;
+      if (entry) entry[at] = exact_word(kb, g0, g1, kfirst, r.f0, r.f1, attends);
     }
-    if (k1) {
-      if (col_idx) col_idx[at[1]] = kb;
-      if (entry) entry[at[1]] = exact_entry(kb, rt.b0, rt.b1, c.T, P, B, N, attends);
-    }
-    __syncthreads();
   }
 }
 
@@ -221,12 +196,9 @@ hipError_t launch_build_mask_device(const FrameCfg& c, int32_t P, int32_t B,
                                     int32_t* d_row_ptr, int32_t* d_col_idx,
                                     uint32_t* d_entry, hipStream_t stream) {
   const int32_t nb = (int32_t)((mask_tokens(c, P) + B - 1) / B);
-  const int32_t npairs = (nb + 1) / 2;
-  hipLaunchKernelGGL(count_rows_kernel, dim3(npairs), dim3(kRowThreads), 0, stream, c, P, B,
-                     d_row_ptr);
-  hipLaunchKernelGGL(scan_rows_kernel, dim3(1), dim3(kScanThreads), 0, stream, nb, d_row_ptr);
-  hipLaunchKernelGGL(fill_rows_kernel, dim3(npairs), dim3(kRowThreads), 0, stream, c, P, B,
-                     d_row_ptr, d_col_idx, d_entry);
+  const int32_t rows = ceil_div(nb, kGroups);
+  hipLaunchKernelGGL(build_rows_kernel, dim3(ceil_div(nb, rows)), dim3(kThreads), 0, stream, c, P,
+                     B, rows, d_row_ptr, d_col_idx, d_entry);
   return hipGetLastError();
 }
 
