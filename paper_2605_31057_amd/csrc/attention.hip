@@ -330,18 +330,19 @@ struct WaveState {
 // -inf.  `valid` = N - the wave's first key (at most 0: no key is valid).  Per
 // score one compare of a constant into VCC and one select, a scheduling
 // barrier every 4 scores so that few compare results are live at once.
-template <int NU>
+// For the 16-key tiles KT0 .. KT0 + KTN - 1, whose first key `valid` counts from.
+template <int NU, int KT0 = 0, int KTN = 2 * NU>
 __device__ __forceinline__ void mask_tail(Scores<NU>& sc, int lane, int valid) {
-  if (valid < 32 * NU) {
+  if (valid < 16 * KTN) {
     const int lim = valid - 4 * (lane / 16);   // key 4*(lane/16) + c is valid iff c < lim
 #pragma unroll
-    for (int kt = 0; kt < 2 * NU; ++kt)
+    for (int kt = 0; kt < KTN; ++kt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         if (r % 2 == 0) __builtin_amdgcn_sched_barrier(0);
         const bool ok = 16 * kt + r < lim;
-        sc.s[kt][0][r] = ok ? sc.s[kt][0][r] : -__builtin_inff();
-        sc.s[kt][1][r] = ok ? sc.s[kt][1][r] : -__builtin_inff();
+        sc.s[KT0 + kt][0][r] = ok ? sc.s[KT0 + kt][0][r] : -__builtin_inff();
+        sc.s[KT0 + kt][1][r] = ok ? sc.s[KT0 + kt][1][r] : -__builtin_inff();
       }
   }
 }
@@ -505,12 +506,39 @@ __device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& s
 // P(j) (one MFMA per 32 keys and query tile, `ones` its A operand); then
 // O += P(j) V(j) and S(j+1) = K(j+1) Q^T into `sc`, with K and V fragments
 // read AHEAD fragments early.  The row-sum MFMAs come first: their operands are already in
-// registers, so they run while the first fragments arrive from LDS.
-template <int NU, int RSUM>
+// registers, so they run while the first fragments arrive from LDS.  SKIP: the
+// step is two key blocks (two halves of the key groups), and `keep` says which
+// of them the wave's query block keeps; V of the other is left out, so that
+// what the keys of a key block hold that a query block does not keep (inf, NaN)
+// never reaches it.
+template <int NU, int RSUM, bool SKIP>
 __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
                                            const bf16x8 (&qf)[4][2], Scores<NU>& sc,
                                            const Probs<NU>& pr, WaveState& st,
-                                           const FragAddr& fa, const bf16x8& ones) {
+                                           const FragAddr& fa, const bf16x8& ones, int keep) {
+  if constexpr (SKIP) {
+    if (keep != 3) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        if (!((keep >> (u / (NU / 2))) & 1)) continue;
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+          st.lt[qt] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pr.p[u][qt], st.lt[qt], 0, 0, 0);
+        }
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) {
+          const bf16x8 f = v_frag(lds_v, fa, dt, u);
+#pragma unroll
+          for (int qt = 0; qt < 2; ++qt)
+            st.o[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, pr.p[u][qt], st.o[dt][qt],
+                                                                   0, 0, 0);
+        }
+      }
+      compute_scores<NU>(lds_k, qf, sc, fa);
+      return;
+    }
+  }
   constexpr int NS = 8 * NU;   // K fragments: (key tile, d-step)
   constexpr int NP = 8 * NU;   // V fragments: (d tile, 32-key group)
   constexpr int NF = NS + NP;
@@ -706,6 +734,67 @@ __device__ __forceinline__ int32_t merge_pair(WalkLds& L, uint32_t* stage,
   return __builtin_amdgcn_readfirstlane(min(words, WALK_CAP));
 }
 
+// Merges four CSR rows (entries rp[i] .. rp[i+1]-1) into L.w, largest key first:
+// a bitmap of every row's key blocks in `stage`, and a key block's position is
+// the number of blocks above it in their union.  Words: kb in bits 0..27, bit
+// 28 + i set when row i keeps kb; entries outside [0, nb) are skipped, and at
+// most WALK_CAP entries of a row are read.  Returns the number of words (starts
+// and ends with a barrier).
+__device__ __forceinline__ int32_t merge_four(WalkLds& L, uint32_t* stage,
+                                              const uint32_t* __restrict__ rows,
+                                              const int32_t (&rp)[5], int32_t nb) {
+  constexpr int WORDS = 256;                 // of 32 key blocks: WALK_CAP / 32, rounded up
+  static_assert(WORDS * 32 >= WALK_CAP, "bitmap size");
+  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+  uint32_t* const bm = stage;                // [row][word]
+  uint32_t* const all = stage + 4 * WORDS;   // union
+  int32_t* const above = (int32_t*)(stage + 5 * WORDS);   // blocks in the words after this one
+  __syncthreads();   // the stage buffers are idle
+  for (int t = tid; t < 4 * WORDS; t += Tile::NT) bm[t] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    for (int t = max(rp[i], rp[i + 1] - WALK_CAP) + tid; t < rp[i + 1]; t += Tile::NT) {
+      const uint32_t kb = rows[t];
+      if (kb < (uint32_t)nb) atomicOr(&bm[i * WORDS + kb / 32], 1u << (kb % 32));
+    }
+  __syncthreads();
+  // Threads 0..255 hold the words last to first; blocks before a thread's
+  // word in that order are the blocks above it.
+  const int w = WORDS - 1 - tid;
+  int cnt = 0, incl = 0;
+  if (tid < WORDS) {
+    const uint32_t u = bm[w] | bm[WORDS + w] | bm[2 * WORDS + w] | bm[3 * WORDS + w];
+    all[w] = u;
+    cnt = __popc(u);
+    incl = cnt;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int y = __shfl_up(incl, off);
+      if (lane >= off) incl += y;
+    }
+    if (lane == 63) L.cnt[0][wave][0] = incl;
+  }
+  __syncthreads();
+  int words = 0;
+  for (int v = 0; v < WORDS / 64; ++v) {
+    const int c = L.cnt[0][v][0];
+    if (v < wave) incl += c;
+    words += c;
+  }
+  if (tid < WORDS) above[w] = incl - cnt;
+  __syncthreads();
+  for (int kb = tid; kb < nb; kb += Tile::NT) {
+    const uint32_t rest = all[kb / 32] >> (kb % 32);   // this block and those above it
+    if (!(rest & 1u)) continue;
+    uint32_t word = (uint32_t)kb;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) word |= ((bm[i * WORDS + kb / 32] >> (kb % 32)) & 1u) << (28 + i);
+    L.w[above[kb / 32] + __popc(rest >> 1)] = word;
+  }
+  __syncthreads();   // the words are written; the stage buffers are free again
+  return __builtin_amdgcn_readfirstlane(words);
+}
+
 // The step words of a tile that lies in one query block: its CSR row, largest
 // key first.  Returns the number of words (ends with a barrier).
 template <bool EXACT>
@@ -802,10 +891,14 @@ __device__ __forceinline__ void attn_tile(
   constexpr int NU = SP::NU;
   constexpr bool SPARSE = MODE != ATTN_DENSE;
   constexpr bool EXACT = MODE == ATTN_EXACT;
-  constexpr bool PAIR = SP::ROWS > BLOCK;        // two query blocks, else (part of) one
+  constexpr bool QUAD = SP::ROWS == 4 * BLOCK;   // four query blocks
+  constexpr bool PAIR = SP::ROWS == 2 * BLOCK;   // two of them, else (part of) one
   constexpr int SUBS = TL::KEYS / BLOCK;         // key blocks per step
-  static_assert(SP::ROWS <= 2 * BLOCK, "a tile covers at most two query blocks");
-  static_assert(SP::NK <= BLOCK, "a wave's keys lie in one key block");
+  // Four query blocks only in the block form: four 4-bit patterns and a key
+  // block do not fit the token-exact form's words.
+  static_assert(QUAD ? MODE == ATTN_BLOCK && SUBS == 2 : SP::ROWS <= 2 * BLOCK, "tile rows");
+  static_assert(QUAD || SP::NK <= BLOCK, "a wave's keys lie in one key block");
+  constexpr uint32_t KB_MASK = EXACT ? 0xFFFFu : QUAD ? 0x0FFFFFFFu : 0x3FFFFFFFu;
   const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void*)lds;
 
   const int tid = threadIdx.x;
@@ -832,10 +925,9 @@ __device__ __forceinline__ void attn_tile(
   const uint32_t v_bytes = (uint32_t)(((int64_t)(N - 1) * v_st + D) * 2);
   const LoadPlan kp = load_plan<BLOCK>((uint32_t)(k_st * 2), wave, lane);
   const LoadPlan vp = load_plan<BLOCK>((uint32_t)(v_st * 2), wave, lane);
-  // Step words: key block in bits 0..29 (block form) or 0..15 (exact form).
-  auto kb_of = [&](uint32_t w) {
-    return (int)(EXACT ? (w & 0xFFFFu) : (w & 0x3FFFFFFFu));
-  };
+  // Step words: key block in bits 0..29 (block form; 0..27 with four query
+  // blocks) or 0..15 (exact form).
+  auto kb_of = [&](uint32_t w) { return (int)(w & KB_MASK); };
   auto rk_at = [&](uint32_t w) {
     return tile_rsrc<BLOCK>(kh_base, k_st, k_bytes, kb_of(w), nb);
   };
@@ -889,7 +981,7 @@ __device__ __forceinline__ void attn_tile(
   // no CSR (row_ptr null, nb <= WALK_CAP): the same code as a full mask's
   // walk, without the merge.
   auto dense_word = [&](int i) {
-    return i < nb ? (uint32_t)(nb - 1 - i) | 0xC0000000u : 0x3FFFFFFFu;
+    return i < nb ? (uint32_t)(nb - 1 - i) | ~KB_MASK : KB_MASK;
   };
   auto dense_words = [&]() {
     __syncthreads();
@@ -900,7 +992,13 @@ __device__ __forceinline__ void attn_tile(
     if (EXACT || row_ptr != nullptr) {
       const int32_t r0 = __builtin_amdgcn_readfirstlane(row_ptr[qb0]);
       const int32_t r1 = __builtin_amdgcn_readfirstlane(row_ptr[qb0 + 1]);
-      if constexpr (PAIR) {
+      if constexpr (QUAD) {
+        int32_t rp[5] = {r0, r1, 0, 0, 0};
+#pragma unroll
+        for (int i = 2; i < 5; ++i)
+          rp[i] = __builtin_amdgcn_readfirstlane(row_ptr[min(qb0 + i, nb)]);
+        words = merge_four(walk, (uint32_t*)lds, rows, rp, nb);
+      } else if constexpr (PAIR) {
         const int32_t r2 =
             qb0 + 1 < nb ? __builtin_amdgcn_readfirstlane(row_ptr[qb0 + 2]) : r1;
         words = merge_pair<TL::NT, EXACT>(walk, (uint32_t*)lds, rows, r0, r1, r1, r2, nb);
@@ -917,7 +1015,7 @@ __device__ __forceinline__ void attn_tile(
     // An odd walk ends with a word that no query block keeps and whose loads
     // read zeros (words < WALK_CAP, which is even).
     if (words & 1) {
-      if (tid == 0 && words < WALK_CAP) walk.w[words] = EXACT ? 0xFFFFu : 0x3FFFFFFFu;
+      if (tid == 0 && words < WALK_CAP) walk.w[words] = KB_MASK;
       __syncthreads();
     }
   }
@@ -927,6 +1025,14 @@ __device__ __forceinline__ void attn_tile(
     w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[sub]);
     w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[SUBS * min(1, n - 1) + sub]);
     w2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[SUBS * min(2, n - 1) + sub]);
+  }
+  // With four query blocks a wave takes the keys of both key blocks of a step:
+  // the words of the one it does not load.
+  uint32_t o0 = 0u, o1 = 0u, o2 = 0u;
+  if (QUAD && n > 0) {
+    o0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[1 - sub]);
+    o1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[SUBS * min(1, n - 1) + 1 - sub]);
+    o2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)walk.w[SUBS * min(2, n - 1) + 1 - sub]);
   }
 
   WaveState ws;
@@ -966,13 +1072,28 @@ __device__ __forceinline__ void attn_tile(
     asm("" : "+v"(lead_v));
     const bool lead = lead_v != 0;
     auto second = [&](bool follower) { return PAIR && (KG == 1 ? follower : qb > qb0); };
+    // Masks a step's scores: its key block, or with four query blocks its two
+    // (returns which of them the wave's query block keeps).
+    auto mask_step = [&](Scores<NU>& sc, uint32_t w, uint32_t o, bool follower) -> int {
+      if constexpr (QUAD) {
+        const uint32_t wa = sub ? o : w, wb = sub ? w : o;
+        const int bit = __builtin_amdgcn_readfirstlane(28 + qb - qb0);
+        const int ka = (wa >> bit) & 1u, kb = (wb >> bit) & 1u;
+        mask_tail<NU, 0, NU>(sc, lane, ka ? N - kb_of(wa) * BLOCK : 0);
+        mask_tail<NU, NU, NU>(sc, lane, kb ? N - kb_of(wb) * BLOCK : 0);
+        return ka | kb << 1;
+      } else {
+        mask_block(sc, w, second(follower));
+        return 3;
+      }
+    };
     issue_tile(k_slot0, rk_at(w0), kp);
     issue_tile(v_slot0, rv_at(w0), vp);
     issue_tile(k_slot0 + TL::BYTES, rk_at(w1), kp);
     wait_loads_and_sync();
     Scores<NU> sc;
     compute_scores<NU>(k_lds, qf, sc, fa);   // S(0)
-    mask_block(sc, w0, second(upper));
+    int keep = mask_step(sc, w0, o0, upper);
     Probs<NU> pr;
     if (lead) softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, nullptr);   // P(0)
     __syncthreads();
@@ -982,6 +1103,7 @@ __device__ __forceinline__ void attn_tile(
       // walk never passes WALK_CAP words, nb <= WALK_CAP).
       const int g3 = SUBS * min(j + 3, n - 1) + sub;
       const uint32_t w3v = walk.w[min(g3, WALK_CAP - 1)];
+      const uint32_t o3v = QUAD ? walk.w[min(g3 ^ 1, WALK_CAP - 1)] : 0u;
       const StepLoads sl{
           (uint32_t)__builtin_amdgcn_readfirstlane(k_slot0 + (uint32_t)(j & 1) * TL::BYTES),
           (uint32_t)__builtin_amdgcn_readfirstlane(v_slot0 + (uint32_t)((j + 1) & 1) * TL::BYTES),
@@ -990,8 +1112,8 @@ __device__ __forceinline__ void attn_tile(
       const char* const vj = v_lds + (j & 1) * TL::BYTES;          // V(j)
       // half-period 2j
       if (lead) {
-        gemm_phase<NU, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones);
-        mask_block(sc, w1, second(false));
+        gemm_phase<NU, RSUM, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep);
+        keep = mask_step(sc, w1, o1, false);
       } else {
         if constexpr (KG == 1) issue_step_loads(sl);
         softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, KG == 1 ? nullptr : &sl);
@@ -1004,11 +1126,15 @@ __device__ __forceinline__ void attn_tile(
           softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, nullptr);
         }
       } else {
-        gemm_phase<NU, RSUM>(kj1, vj, qf, sc, pr, ws, fa, ones);
-        mask_block(sc, w1, second(true));
+        gemm_phase<NU, RSUM, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep);
+        keep = mask_step(sc, w1, o1, true);
       }
       wait_loads_and_sync();
       w1 = w2;
+      if constexpr (QUAD) {
+        o1 = o2;
+        o2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)o3v);
+      }
       w2 = SPARSE || g3 < WALK_CAP ? (uint32_t)__builtin_amdgcn_readfirstlane((int)w3v)
                                    : dense_word(g3);
     }
@@ -1213,28 +1339,30 @@ int tiles_of(const AttnArgs& a, int kg) {
 // 128-row items, 7.48 and 42.7 ms in 64-row items; with 64-token blocks 10.8
 // against 13.7 ms).  So whole tiles fill all rounds but the last one or two,
 // and what remains is split if that ends earlier.
-Plan make_plan(const AttnArgs& a, int block, int cus) {
-  struct Kind { int kgw, kgs; double whole, part; };
-  static const Kind kinds128[] = {{1, 2, 1.0, 0.60}, {1, 4, 1.0, 0.42}, {2, 4, 0.60, 0.42}};
-  static const Kind kinds64[] = {{2, 4, 1.0, 0.64}};
-  const Kind* const kinds = block == 128 ? kinds128 : kinds64;
-  const int nkinds = block == 128 ? 3 : 1;
-  const int tiles0 = tiles_of(a, kinds[0].kgw);
-  Plan best{kinds[0].kgw, kinds[0].kgs, tiles0};
+// 64-token blocks split the same way; in the token-exact form, whose step words
+// hold two query blocks at most, 128-row tiles into 64-row ones.
+Plan make_plan(const AttnArgs& a, int block, AttnMode mode, int cus) {
+  struct Kind {
+    int kgw, kgs;
+    double part;   // time of a part, in whole tiles' times
+  };
+  static const Kind kinds[] = {{1, 2, 0.60}, {1, 4, 0.42}, {2, 4, 0.64}};
+  const bool half = block == 64 && mode == ATTN_EXACT;
+  const int from = half ? 2 : 0, to = half ? 3 : 2;
+  const int tiles = tiles_of(a, kinds[from].kgw), rounds = tiles / cus;
+  Plan best{kinds[from].kgw, kinds[from].kgs, tiles};
   // A split has to gain 1% to be taken.
-  double best_cost = 0.99 * ((tiles0 + cus - 1) / cus);
-  for (int i = 0; i < nkinds; ++i) {
-    const Kind& k = kinds[i];
-    const int tiles = tiles_of(a, k.kgw), rounds = tiles / cus;
+  double best_cost = 0.99 * ((tiles + cus - 1) / cus);
+  for (int i = from; i < to; ++i)
     for (int w = rounds; w >= 0 && w >= rounds - 1; --w) {
+      const Kind& k = kinds[i];
       const int64_t parts = (int64_t)(tiles - w * cus) * (k.kgs / k.kgw);
-      const double cost = w * k.whole + (double)((parts + cus - 1) / cus) * k.part;
+      const double cost = w + (double)((parts + cus - 1) / cus) * k.part;
       if (cost < best_cost) {
         best_cost = cost;
         best = Plan{k.kgw, k.kgs, w * cus};
       }
     }
-  }
   return best;
 }
 
@@ -1289,16 +1417,16 @@ hipError_t launch_attention(const AttnArgs& a, int32_t block, AttnMode mode,
   if (mode == ATTN_DENSE)
     return block == 128 ? launch_t<128, ATTN_DENSE, 1, 1>(a, tiles_of(a, 1), stream)
                         : launch_t<64, ATTN_DENSE, 2, 2>(a, tiles_of(a, 2), stream);
-  const Plan p = make_plan(a, block, cu_count());
-  if (block == 64)
-    return mode == ATTN_EXACT ? launch_t<64, ATTN_EXACT, 2, 4>(a, p.whole, stream)
-                              : launch_t<64, ATTN_BLOCK, 2, 4>(a, p.whole, stream);
+  const Plan p = make_plan(a, block, mode, cu_count());
+  if (block == 64) {
+    if (mode == ATTN_EXACT) return launch_t<64, ATTN_EXACT, 2, 4>(a, p.whole, stream);
+    if (p.kgs == 4) return launch_t<64, ATTN_BLOCK, 1, 4>(a, p.whole, stream);
+    return launch_t<64, ATTN_BLOCK, 1, 2>(a, p.whole, stream);
+  }
   if (mode == ATTN_EXACT) {
-    if (p.kgw == 2) return launch_t<128, ATTN_EXACT, 2, 4>(a, p.whole, stream);
     if (p.kgs == 4) return launch_t<128, ATTN_EXACT, 1, 4>(a, p.whole, stream);
     return launch_t<128, ATTN_EXACT, 1, 2>(a, p.whole, stream);
   }
-  if (p.kgw == 2) return launch_t<128, ATTN_BLOCK, 2, 4>(a, p.whole, stream);
   if (p.kgs == 4) return launch_t<128, ATTN_BLOCK, 1, 4>(a, p.whole, stream);
   return launch_t<128, ATTN_BLOCK, 1, 2>(a, p.whole, stream);
 }

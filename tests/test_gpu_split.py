@@ -1,0 +1,153 @@
+"""GPU parity of the launch plans: a launch's tiles run whole (256 query rows)
+or split over the key groups of a workgroup (128 or 64 rows), or whole rounds
+whole and the rest split, by the number of tiles; 64-token blocks take two key
+blocks per step and four query blocks per whole tile.  Shapes on both sides of
+each line of the plan (256 CUs), with ragged ends, over random caller CSRs
+whose rows differ within a tile (some empty), the token-exact form and dense
+attention, against the fp32 oracle on the first and last heads (whole tiles
+come first, split ones last)."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_31057_amd as L
+from paper_2605_31057_amd.inputs import make_qkv
+from oracle import attention as OA
+from oracle import mask as M
+from tests.gpu_util import assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    L.lib()
+
+
+def _say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+def _check(out, ref, heads, N, block):
+    """Heads `heads` of out against block-wise reference rows."""
+    worst, total, count = 0.0, 0.0, 0
+    for (h, qb), r in ref.items():
+        g = out[heads[h], qb * block: qb * block + r.shape[0]].float().cpu().numpy()
+        assert np.isfinite(g).all()
+        err = np.abs(g - r)
+        worst, total, count = max(worst, float(err.max())), total + float(err.sum()), count + err.size
+    assert_close(worst, total / count)
+
+
+def _random_csr(nb, seed, empty):
+    rng = np.random.default_rng(seed)
+    rows = []
+    for qb in range(nb):
+        n = 0 if qb in empty else int(rng.integers(1, nb + 1))
+        rows.append(sorted(rng.choice(nb, size=n, replace=False).tolist()))
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    return rp, np.asarray([k for r in rows for k in r], dtype=np.int32)
+
+
+# heads, tokens: 256-row tiles per launch, and what the plan makes of them.
+SHAPES = [
+    (2, 1),        #   2: 64-row parts, one token
+    (8, 2049),     #  72: 128-row parts, the last part one row
+    (64, 1000),    # 256: whole
+    (37, 1740),    # 259: whole and 64-row parts
+    (40, 2055),    # 360: whole and 128-row parts
+    (66, 1793),    # 528: two rounds whole, 64-row parts
+]
+
+
+@pytest.mark.parametrize("block", [128, 64])
+@pytest.mark.parametrize("H,N", SHAPES)
+def test_random_csr_by_plan(H, N, block):
+    _say(f"[split] block form H={H} N={N} B={block}")
+    q, k, v = make_qkv(H, N, seed=H + N)
+    nb = -(-N // block)
+    empty = {nb // 2} if nb > 2 else set()
+    rp, ci = _random_csr(nb, H + block, empty)
+    m = L.csr_mask(torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), N, block)
+    out = torch.full((H, N, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    L.attention(q.cuda(), k.cuda(), v.cuda(), m, out=out)
+    dense = L.dense_attention(q.cuda(), k.cuda(), v.cuda(), block=block)
+    torch.cuda.synchronize()
+    heads = sorted({0, H - 1})
+    qs, ks, vs = (x[heads].float().numpy() for x in (q, k, v))
+    ref = OA.block_sparse_attention(qs, ks, vs, rp.tolist(), ci.tolist(), block,
+                                    q_blocks=[qb for qb in range(nb) if qb not in empty])
+    _check(out, ref, heads, N, block)
+    frp, fci = [i * nb for i in range(nb + 1)], list(range(nb)) * nb
+    _check(dense, OA.block_sparse_attention(qs, ks, vs, frp, fci, block), heads, N, block)
+    for qb in empty:
+        assert bool((out[:, qb * block:(qb + 1) * block] == 0).all())
+
+
+@pytest.mark.parametrize("block", [128, 64])
+@pytest.mark.parametrize("H,T,P,text", [(3, 5, 131, 0), (37, 9, 193, 3), (66, 8, 201, 60)])
+def test_exact_by_plan(H, T, P, text, block):
+    _say(f"[split] exact form H={H} T={T} P={P} text={text} B={block}")
+    N = T * P + text
+    q, k, v = make_qkv(H, N, seed=H + N)
+    csr = L.build_mask(T, P, block, 3, L.Params(window=1, tper=4, text_tokens=text), exact=True)
+    csr.upload()
+    out = L.attention_exact(q.cuda(), k.cuda(), v.cuda(), csr.exact_mask())
+    torch.cuda.synchronize()
+    _, _, A = M.attended_frames(T, 3, W=1, tper=4)
+    seg = np.minimum(np.arange(N) // P, T)
+    att = np.ones((T + 1, T + 1), dtype=bool)
+    for t in range(T):
+        att[t, :T] = [u in A[t] for u in range(T)]
+    keep = att[seg][:, seg]
+    worst, total, count = 0.0, 0.0, 0
+    for h in (0, H - 1):
+        s = (q[h].float() @ k[h].float().t()).numpy() / np.sqrt(128.0)
+        s = np.where(keep, s, -np.inf)
+        p = np.exp(s - s.max(1, keepdims=True))
+        err = np.abs(out[h].float().cpu().numpy() -
+                     (p / p.sum(1, keepdims=True)) @ v[h].float().numpy())
+        worst, total, count = max(worst, float(err.max())), total + float(err.sum()), count + err.size
+    assert_close(worst, total / count)
+
+
+@pytest.mark.parametrize("peak", [0.0, 400.0])
+def test_reference_is_raised_within_a_walk(peak):
+    """Scores that grow along the walk (the walk goes from the last key block
+    to the first): the reference is raised by far more than its headroom, step
+    after step, and again for one outlying key near the end."""
+    H, N = 3, 1500
+    q, k, v = make_qkv(H, N, seed=4)
+    k *= torch.linspace(40.0, 0.1, N).view(1, N, 1).to(torch.bfloat16)
+    if peak:
+        k[:, 7] = (q[:, 700] * (peak / 128.0)).to(torch.bfloat16)
+    out = L.dense_attention(q.cuda(), k.cuda(), v.cuda())
+    torch.cuda.synchronize()
+    nb = -(-N // 128)
+    ref = OA.block_sparse_attention(q.float().numpy(), k.float().numpy(), v.float().numpy(),
+                                    [i * nb for i in range(nb + 1)], list(range(nb)) * nb, 128)
+    _check(out, ref, list(range(H)), N, 128)
+
+
+def test_unkept_key_blocks_do_not_reach_a_query_block():
+    """Four 64-token query blocks share a tile; V of a key block that only the
+    first of them keeps may hold anything."""
+    H, N, block = 40, 64 * 29, 64
+    nb = N // block
+    q, k, v = make_qkv(H, N, seed=8)
+    v[:, 5 * block:6 * block] = float("nan")
+    keep = [[kb for kb in range(nb) if kb != 5 or qb % 4 == 0] for qb in range(nb)]
+    rp = torch.tensor([0] + np.cumsum([len(r) for r in keep]).tolist(), dtype=torch.int32)
+    ci = torch.tensor([kb for r in keep for kb in r], dtype=torch.int32)
+    m = L.csr_mask(rp.cuda(), ci.cuda(), N, block)
+    out = L.attention(q.cuda(), k.cuda(), v.cuda(), m)
+    torch.cuda.synchronize()
+    bad = torch.isnan(out.float()).any(-1).view(H, nb, block).any(-1).any(0).cpu().tolist()
+    # Whole tiles (all but the last head's, which may be split) keep them apart.
+    assert bad[0::4] == [True] * len(bad[0::4])
+    assert not any(bad[i] for i in range(nb) if i % 4 in (2, 3))
