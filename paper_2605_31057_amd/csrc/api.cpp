@@ -594,6 +594,8 @@ lvsa_status attention_args(const lvsa_tensor* q, const lvsa_tensor* k,
 // Launches with a counter set of the pool (lvsa.h, "Tile counters").
 lvsa_status run_attention(AttnArgs& a, int32_t block, AttnMode mode, void* stream) {
   hipStream_t s = (hipStream_t)stream;
+  if (!attention_uses_counters(a, block, mode))
+    return launch_attention(a, block, mode, s) == hipSuccess ? LVSA_OK : LVSA_EDEVICE;
   CounterLease lease;
   const lvsa_status st = acquire_counters(s, &lease);
   if (st != LVSA_OK) return st;

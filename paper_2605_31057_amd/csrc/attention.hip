@@ -1366,13 +1366,21 @@ Plan make_plan(const AttnArgs& a, int block, AttnMode mode, int cus) {
   return best;
 }
 
+// Items of a launch with that plan, and whether it runs a workgroup for every
+// one of them (all whole or all parts): then it takes no counters.
+int plan_items(const AttnArgs& a, const Plan& p) {
+  return p.whole + (tiles_of(a, p.kgw) - p.whole) * (p.kgs / p.kgw);
+}
+bool plan_is_direct(const AttnArgs& a, const Plan& p, int cus) {
+  const int items = plan_items(a, p);
+  return items <= cus && (p.whole == 0 || p.whole == items);
+}
+
 template <int BLOCK, int MODE, int KGW, int KGS>
-hipError_t launch_t(const AttnArgs& a, int whole, hipStream_t stream) {
+hipError_t launch_t(const AttnArgs& a, const Plan& p, hipStream_t stream) {
   const float scale_log2 = 1.4426950408889634f / __builtin_sqrtf((float)D);
   const int per_head = (int)(((int64_t)a.n_tokens + Split<KGW>::ROWS - 1) / Split<KGW>::ROWS);
-  const int tiles = per_head * a.heads;
-  const int split = (tiles - whole) * (KGS / KGW);
-  const int items = whole + split;
+  const int items = plan_items(a, p);
   // One persistent workgroup per CU (each takes 160 KB of LDS, so one fits a
   // CU), or one per item when there are fewer items.
   const int grid = items < cu_count() ? items : cu_count();
@@ -1385,11 +1393,11 @@ hipError_t launch_t(const AttnArgs& a, int whole, hipStream_t stream) {
   k.v_sh = a.v_sh; k.v_st = a.v_st; k.o_sh = a.o_sh; k.o_st = a.o_st;
   k.row_ptr = a.row_ptr;
   k.rows = a.rows;
-  k.counters = items <= grid && (whole == 0 || split == 0) ? nullptr : a.counters;
+  k.counters = plan_is_direct(a, p, cu_count()) ? nullptr : a.counters;
   k.N = a.n_tokens; k.nb = a.n_blocks; k.P = a.frame_tokens;
   k.per_head = per_head;
-  k.whole = whole;
-  k.split = split;
+  k.whole = p.whole;
+  k.split = items - p.whole;
   k.scale_log2 = scale_log2;
   if (k.counters)
     hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, stream, a.counters);
@@ -1400,35 +1408,51 @@ hipError_t launch_t(const AttnArgs& a, int whole, hipStream_t stream) {
 
 }  // namespace
 
+namespace {
+
+// Dense attention over at most WALK_CAP key blocks runs the block mode's
+// kernel without a CSR: the same code as the block-sparse kernel with a full
+// mask, which it matched or beat only that way (a separate dense instantiation
+// timed 0.6% slower than the full-mask launch at the Wan-1.3B 6x shape,
+// interleaved on one board, for no difference in its step loop but the layout
+// of its branches).
+AttnMode kernel_mode(const AttnArgs& a, AttnMode mode) {
+  return mode == ATTN_DENSE && a.n_blocks <= WALK_CAP ? ATTN_BLOCK : mode;
+}
+
+Plan plan_of(const AttnArgs& a, int32_t block, AttnMode mode) {
+  // Past WALK_CAP key blocks: whole tiles only.
+  if (mode == ATTN_DENSE) {
+    const int kg = block == 128 ? 1 : 2;
+    return Plan{kg, kg, tiles_of(a, kg)};
+  }
+  return make_plan(a, block, mode, cu_count());
+}
+
+}  // namespace
+
+bool attention_uses_counters(const AttnArgs& a, int32_t block, AttnMode mode) {
+  return !plan_is_direct(a, plan_of(a, block, kernel_mode(a, mode)), cu_count());
+}
+
 hipError_t launch_attention(const AttnArgs& a, int32_t block, AttnMode mode,
                             hipStream_t stream) {
-  // Dense attention over at most WALK_CAP key blocks runs the block mode's
-  // kernel without a CSR: the same code as the block-sparse kernel with a
-  // full mask, which it matched or beat only that way (the separate dense
-  // instantiation timed 0.6% slower than the full-mask launch at the
-  // Wan-1.3B 6x shape, interleaved on one board, for no difference in its
-  // step loop but the layout of its branches).
-  if (mode == ATTN_DENSE && a.n_blocks <= WALK_CAP) {
-    AttnArgs d = a;
-    d.row_ptr = nullptr;
-    d.rows = nullptr;
-    return launch_attention(d, block, ATTN_BLOCK, stream);
-  }
+  mode = kernel_mode(a, mode);
+  const Plan p = plan_of(a, block, mode);
   if (mode == ATTN_DENSE)
-    return block == 128 ? launch_t<128, ATTN_DENSE, 1, 1>(a, tiles_of(a, 1), stream)
-                        : launch_t<64, ATTN_DENSE, 2, 2>(a, tiles_of(a, 2), stream);
-  const Plan p = make_plan(a, block, mode, cu_count());
+    return block == 128 ? launch_t<128, ATTN_DENSE, 1, 1>(a, p, stream)
+                        : launch_t<64, ATTN_DENSE, 2, 2>(a, p, stream);
   if (block == 64) {
-    if (mode == ATTN_EXACT) return launch_t<64, ATTN_EXACT, 2, 4>(a, p.whole, stream);
-    if (p.kgs == 4) return launch_t<64, ATTN_BLOCK, 1, 4>(a, p.whole, stream);
-    return launch_t<64, ATTN_BLOCK, 1, 2>(a, p.whole, stream);
+    if (mode == ATTN_EXACT) return launch_t<64, ATTN_EXACT, 2, 4>(a, p, stream);
+    if (p.kgs == 4) return launch_t<64, ATTN_BLOCK, 1, 4>(a, p, stream);
+    return launch_t<64, ATTN_BLOCK, 1, 2>(a, p, stream);
   }
   if (mode == ATTN_EXACT) {
-    if (p.kgs == 4) return launch_t<128, ATTN_EXACT, 1, 4>(a, p.whole, stream);
-    return launch_t<128, ATTN_EXACT, 1, 2>(a, p.whole, stream);
+    if (p.kgs == 4) return launch_t<128, ATTN_EXACT, 1, 4>(a, p, stream);
+    return launch_t<128, ATTN_EXACT, 1, 2>(a, p, stream);
   }
-  if (p.kgs == 4) return launch_t<128, ATTN_BLOCK, 1, 4>(a, p.whole, stream);
-  return launch_t<128, ATTN_BLOCK, 1, 2>(a, p.whole, stream);
+  if (p.kgs == 4) return launch_t<128, ATTN_BLOCK, 1, 4>(a, p, stream);
+  return launch_t<128, ATTN_BLOCK, 1, 2>(a, p, stream);
 }
 
 }  // namespace lvsa

@@ -41,16 +41,17 @@ hipError_t launch_build_mask_device(const FrameCfg& c, int32_t P, int32_t B,
                                     int32_t* d_row_ptr, int32_t* d_col_idx,
                                     uint32_t* d_entry, hipStream_t stream);
 
-// Key blocks a sparse attention launch supports: a workgroup merges the two
-// CSR rows of its pair of query blocks (at most nb words) in LDS.
+// Key blocks a sparse attention launch supports: a workgroup merges the CSR
+// rows of its tile's query blocks (at most nb words) in LDS.
 constexpr int32_t kMaxSparseBlocks = 8000;
 
 // Tile counters of one attention launch: eight 64-bit words (one per XCD),
-// zeroed on the launch stream before the kernel runs.
+// zeroed on the launch stream before the kernel runs.  Launches with a
+// workgroup for every tile take none.
 constexpr int kTileCounters = 8;
 
 // Attention launch (attention.hip).  Pointers are bf16 tensors; strides in
-// elements.  The sparse modes read the CSR rows of each pair of query blocks
+// elements.  The sparse modes read the CSR rows of each tile's query blocks
 // (col_idx for ATTN_BLOCK, entry words for ATTN_EXACT); row_ptr and rows are
 // null for the dense pass.
 struct AttnArgs {
@@ -70,6 +71,9 @@ struct AttnArgs {
 enum AttnMode { ATTN_DENSE = 0, ATTN_BLOCK = 1, ATTN_EXACT = 2 };
 hipError_t launch_attention(const AttnArgs& a, int32_t block, AttnMode mode,
                             hipStream_t stream);
+// Whether that launch takes tile counters (one with a workgroup for every tile
+// does not; `counters` is then unused).
+bool attention_uses_counters(const AttnArgs& a, int32_t block, AttnMode mode);
 
 // Per-device pool of tile-counter sets (api.cpp).  acquire hands out a set no
 // launch in flight uses; release records, after the launch on `stream`, the

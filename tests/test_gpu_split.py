@@ -151,3 +151,30 @@ def test_unkept_key_blocks_do_not_reach_a_query_block():
     # Whole tiles (all but the last head's, which may be split) keep them apart.
     assert bad[0::4] == [True] * len(bad[0::4])
     assert not any(bad[i] for i in range(nb) if i % 4 in (2, 3))
+
+
+def test_counted_launches_in_graphs_and_streams():
+    """A launch of more tiles than CUs takes tile counters: captured and
+    replayed it gives the eager bits, also beside eager launches on another
+    stream."""
+    H, N, block = 70, 1000, 128
+    q, k, v = (x.cuda() for x in make_qkv(H, N, seed=12))
+    nb = -(-N // block)
+    rp, ci = _random_csr(nb, 5, set())
+    m = L.csr_mask(torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), N, block)
+    want = L.attention(q, k, v, m)
+    out, other = torch.empty_like(q), torch.empty_like(q)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        L.attention(q, k, v, m, out=out, stream=torch.cuda.current_stream())
+    for rep in range(4):
+        out.fill_(float("nan"))
+        other.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        L.attention(q, k, v, m, out=other, stream=side)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), f"replay {rep}"
+        assert torch.equal(other, want), f"eager launch beside replay {rep}"
