@@ -300,9 +300,10 @@ typedef struct lvsa_tensor {
 } lvsa_tensor;
 
 /* Tile counters.  The attention kernels run one persistent workgroup per
- * compute unit; workgroups take tiles (a head and two adjacent query blocks)
- * through atomic counters, eight per launch (one per XCD), so XCDs that
- * clock faster take on more tiles.  Every launch gets counters of its own
+ * compute unit; workgroups take tiles (256 query rows of a head, or parts of
+ * that) through atomic counters, eight per launch (one per XCD), so XCDs that
+ * clock faster take on more tiles.  A launch with a workgroup for every tile
+ * needs none.  Every other launch gets counters of its own
  * from a per-device pool the library owns (a few KB, allocated on the first
  * launch on a device and grown when every counter set is still in use), zeroed
  * by a small kernel on the launch stream before the attention kernel runs and
@@ -318,11 +319,11 @@ typedef struct lvsa_tensor {
  * block of i.  bf16 inputs, fp32 products and softmax, bf16 output (round to
  * nearest even).  q, k, v, out share heads, n_tokens = mask->n_tokens and
  * head_dim = 128; mask->block is 64 or 128 and mask->n_q_blocks =
- * mask->n_kv_blocks = ceil(N / B) <= 8000 (a workgroup merges the two CSR
- * rows of its pair of query blocks in LDS).  Rows i >= N of `out` are never written;
+ * mask->n_kv_blocks = ceil(N / B) <= 8000 (a workgroup merges the CSR rows of
+ * its tile's query blocks in LDS).  Rows i >= N of `out` are never written;
  * a query block whose row is empty gets zeros.  out must not overlap q, k or
- * v.  The result is deterministic (fixed key order per row, whichever
- * workgroup computes it).
+ * v.  The result is deterministic: for given heads, tokens and block, the keys
+ * of a row are taken in a fixed order, whichever workgroup computes it.
  * Errors: EINVAL (nulls, shape mismatch), EUNSUPPORTED (head_dim, block,
  * alignment), ENOMEM (tile counters), EDEVICE (launch). */
 lvsa_status lvsa_attention(const lvsa_tensor* q, const lvsa_tensor* k,

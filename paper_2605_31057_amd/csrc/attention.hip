@@ -5,69 +5,88 @@
 // (all keys) with the same kernel visiting every key block.
 //
 // Work decomposition
-//   A tile is (head, pair of query blocks 2p and 2p+1): 2*BLOCK query rows,
-//   NW = 2*BLOCK/32 waves (8 at BLOCK = 128) of 32 rows each; waves
-//   0..NW/2-1 hold rows of query block 2p, the others rows of 2p+1.  The
-//   workgroup walks the union of the two blocks' key lists one key block per
-//   step, and every wave takes all BLOCK keys of the step for its rows.
-//   Adjacent query blocks mostly keep the same key blocks (they touch the
-//   same frames), so each K/V tile brought from HBM/L2 into LDS serves
-//   2*BLOCK query rows; a key block that only one of the two keeps is masked
-//   out (no valid keys) for the other's waves.  One persistent workgroup per
-//   compute unit takes tiles through atomic counters (fetch_tile).
+//   A whole tile is 256 query rows of one head (two query blocks at BLOCK =
+//   128, four at 64), eight waves of 32 rows each.  The workgroup walks the
+//   union of the query blocks' key lists, 128 keys per step (one key block, or
+//   two of 64), and every wave takes all keys of the step for its rows.
+//   Adjacent query blocks mostly keep the same key blocks (they touch the same
+//   frames), so each K/V tile brought from HBM/L2 into LDS serves 256 query
+//   rows; a key block that only some of the query blocks keep is masked out
+//   (no valid keys) for the waves of the others.
+//   Where whole tiles leave compute units idle (few tiles, or a last round that
+//   is nearly empty), tiles are split over the key groups of a workgroup
+//   (Split): 128 or 64 rows, the eight waves sharing the step's keys as well as
+//   the rows, partial results combined in LDS at the end (combine_groups).  The
+//   host plans which tiles run how (make_plan).
+//   One persistent workgroup per compute unit takes items through atomic
+//   counters (fetch_item); a launch with a workgroup for every item has no
+//   counters.
 //
 // The merged walk
-//   A tile's key blocks are the union of CSR rows 2p and 2p+1, walked in
+//   A tile's key blocks are the union of its query blocks' CSR rows, walked in
 //   descending order, each key block once with a flag per query block.  At
-//   the start of the tile the workgroup merges the two rows in LDS: every
-//   entry's position in the union is its index in its own row plus the
+//   the start of the tile the workgroup merges two rows in LDS (merge_pair):
+//   every entry's position in the union is its index in its own row plus the
 //   entries of the other row above it (a binary search) minus the entries
 //   above it that both rows hold (a ballot count), and the step words are
-//   written there.  The step loop then reads one word per step, three steps
-//   ahead (K tiles are loaded two steps ahead).  The sparse modes take at most
-//   WALK_CAP key blocks (checked before launch), so one merge covers any
-//   pair.  Dense attention up to WALK_CAP key blocks runs the block mode with
-//   no CSR: the words are written directly instead of merged.  The mask is
-//   only read, so any number of launches can share it.
+//   written there; four rows are merged through bitmaps (merge_four), a tile
+//   within one query block takes its row as it is (single_row).  The step loop
+//   then reads its words three steps ahead (K tiles are loaded two steps
+//   ahead).  The sparse modes take at most WALK_CAP key blocks (checked before
+//   launch), so one merge covers any tile.  Dense attention up to WALK_CAP key
+//   blocks runs the block mode with no CSR: the words are written directly
+//   instead of merged.  The mask is only read, so any number of launches can
+//   share it.
 //
-// Schedule ("ping-pong", one key block per step)
-//   Waves w and w + NW/2 (which share a SIMD when NW = 8) run half a step
-//   apart: while one is in its GEMM phase (O += P(j) V(j), S(j+1) = K(j+1)
-//   Q^T: MFMA with fragments from LDS) the other is in its softmax phase (row
-//   max, exponentials, P in bf16: VALU), so the matrix
-//   core and the VALU of each SIMD are busy at the same time.  A barrier ends
-//   every half step.  LDS holds two K stages and two V stages (slab layout,
-//   see below); K(j+2) and V(j+1) stream from HBM/L2 into the stages freed by
-//   step j-1 with buffer loads that write LDS directly, issued during the
-//   first half of step j and waited for at its end.  The buffer resource's
-//   size bound turns rows at or past N (ragged last block) into zeros.
-//   Row sums (RowSums): in the block mode, 64 fp32 adds per step in the
-//   softmax phase; in the other modes the matrix core, where a 16x16x32 MFMA
-//   with a constant 0/1 A operand adds up each 16-key step of P for all 32
-//   rows of the wave in the GEMM phase (8 small MFMAs per step, summing
-//   exactly the bf16 P that multiplies V).
+// Schedule ("ping-pong", 128 keys per step)
+//   Waves w and w + 4 (which share a SIMD) run half a step apart: while one is
+//   in its GEMM phase (O += P(j) V(j), S(j+1) = K(j+1) Q^T: MFMA with fragments
+//   from LDS) the other is in its softmax phase (exponentials, P in bf16:
+//   VALU), so the matrix core and the VALU of each SIMD are busy at the same
+//   time.  A barrier ends every half step.  LDS holds two K stages and two V
+//   stages (slab layout, see below); K(j+2) and V(j+1) stream from HBM/L2 into
+//   the stages freed by step j-1 with buffer loads that write LDS directly,
+//   issued by every wave in its softmax phase and waited for at the end of the
+//   step.  The buffer resource's size bound turns rows at or past N (ragged
+//   last block) into zeros.
 //   A whole key block per step keeps the per-step costs (two barriers, the
-//   loop, the load set-up) small against the step's 72 MFMAs per wave; S
+//   loop, the load set-up) small against the step's 136 MFMAs per wave; S
 //   (64 registers) and P (32) then fill the register file, so the GEMM
 //   phase finishes P(j) before it produces S(j+1), and masks run only in a
-//   wave-uniform branch, one compare into VCC and one select per score.
+//   wave-uniform branch.
 //
-// Contractions (bf16 MFMA 32x32x16, fp32 accumulate)
+// Contractions (bf16 MFMA 16x16x32, fp32 accumulate)
 //     S^T = K Q^T     A = K rows (LDS, ds_read_b128), B = Q rows (registers)
 //     O^T += V^T P^T  A = V^T (LDS, ds_read_b64_tr_b16), B = P (registers)
-//   The transposed products put one query row per lane (lanes l and l^32
-//   share row l%32), so row statistics are in-lane reductions plus one
-//   permlane32 exchange, and P never leaves registers.
-//   MFMA 32x32 lane layout (lane l, half h = l/32, i = l%32): A row i and B
-//   column i carry k-slots 8h..8h+7; C register r holds row 8*(r/4)+4h+(r%4),
-//   column i.  k-slot order only has to agree between A and B, so the key
-//   held by S^T's C register r is paired with the V^T element of that key.
+//   The transposed products put a query row's scores in four lanes (l, l^16,
+//   l^32, l^48), and P never leaves registers.
+//   MFMA 16x16x32 lane layout (lane l, group g = l/16, i = l%16): A row i and B
+//   column i carry k-slots 8g..8g+7; C register r holds row 4g + r, column i.
+//   k-slot order only has to agree between A and B, so the keys held by S^T's
+//   C registers of two 16-key tiles are paired with the V^T elements of those
+//   keys (v_frag).
+//   A wave's 32 query rows are two tiles of 16, and each K or V fragment is used
+//   for both.
 //
-// Online softmax (fp32, base 2): m = running max of s*log2(e)/sqrt(d),
-// p = exp2(s*log2(e)/sqrt(d) - m), l = sum p.  The running max is raised only
-// when a new row max exceeds it by more than 8 (p then stays below 2^8), which
-// skips most rescales of O; the result is exact either way because O and l
-// always use the same m.
+// What bounds it
+//   Board power, then the VALU's issue slots.  The launch draws the board's
+//   limit and the clock drops (2.4 GHz peak; 1.55 GHz with 32x32x16 MFMAs,
+//   1.9 GHz with 16x16x32), so energy per step is time: a stream of 16x16x32
+//   MFMAs on random data, four in a row into one accumulator, reaches 2.19
+//   PFLOP/s at the limit, alternating accumulators 2.06, 32x32x16 1.75-1.84.
+//   In cycles, an MFMA issue blocks the VALU for about 8 (an fma takes 8.3
+//   cycles beside 16x16x32 MFMAs, 4.5 alone; an exponential 16.4 and 8.5), so
+//   the softmax phase (112 VALU instructions and 64 exponentials a step beside
+//   136 MFMAs, and 8 tile loads of about 67 cycles) takes 2,700 cycles, and the
+//   GEMM phase (136 MFMAs of 16 cycles, 96 LDS reads of about 2.3) 2,600.
+//   Wan-1.3B 6x, 12 heads, step 10: 30.7 ms with 32x32x16 MFMAs and a row
+//   maximum per step, 27.6 ms now (1.45 PFLOP/s; a large bf16 matrix product
+//   reaches 1.62 on this card), interleaved on one board.
+//
+// Online softmax (fp32, base 2): p = exp2(s*log2(e)/sqrt(d) - m), l = sum p,
+// with a reference m per row that is raised, and O and l rescaled, only when
+// some p reaches 2 (softmax_phase); the result is exact either way because O
+// and l always use the same m.
 #include <atomic>
 
 #include "internal.h"
@@ -315,7 +334,14 @@ __device__ __forceinline__ void compute_scores(const char* lds_k, const bf16x8 (
 // (register 0 of every lane holds its row's sum), or on the VALU, as a
 // partial sum per lane and query tile of the fp32 probabilities of the lane's
 // own keys that the softmax phase adds into (the four lanes of a row hold
-// its parts).
+// its parts).  Whole tiles use the matrix core: 8 MFMAs instead of 64 adds in
+// the softmax phase, whose VALU slots are the scarcer (1.2-1.4% at Wan 6x and
+// 1x, interleaved).  It sums exactly the P that multiplies V, so the weights
+// of a row add up to 1, and the result is no further from float64 than with
+// fp32 sums: 2-norm of the error relative to
+// the result, dense attention over 4,680 keys of N(0, 1) with Q and K times 1,
+// 2, 4, 8: 2.34e-3, 2.07e-3, 1.75e-3 and 1.07e-3 with fp32 sums, 2.34e-3,
+// 1.87e-3, 1.53e-3 and 0.94e-3 with these.
 enum RowSums { RSUM_MFMA = 0, RSUM_VALU = 1 };
 
 struct WaveState {
