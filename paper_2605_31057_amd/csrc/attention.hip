@@ -46,9 +46,10 @@
 //   time.  A barrier ends every half step.  LDS holds two K stages and two V
 //   stages (slab layout, see below); K(j+2) and V(j+1) stream from HBM/L2 into
 //   the stages freed by step j-1 with buffer loads that write LDS directly,
-//   issued by every wave in its softmax phase and waited for at the end of the
-//   step.  The buffer resource's size bound turns rows at or past N (ragged
-//   last block) into zeros.
+//   issued by every wave in its softmax phase (in split tiles all in the step's
+//   first half, StepLoads) and waited for at the end of the step.  The buffer
+//   resource's size bound turns rows at or past N (ragged last block) into
+//   zeros.
 //   A whole key block per step keeps the per-step costs (two barriers, the
 //   loop, the load set-up) small against the step's 136 MFMAs per wave; S
 //   (64 registers) and P (32) then fill the register file, so the GEMM
@@ -227,15 +228,24 @@ __device__ __forceinline__ void issue_tile(uint32_t lds, __amdgpu_buffer_rsrc_t 
     issue_load(lds + lp.lds_w + 1024u * Tile::NW * j, rsrc, lp.lane_off, 64u * j);
 }
 
-// The loads of one pipeline step: the next K tile and the next V tile.  Every
-// wave issues its share in its softmax phase, which has the slack (a tile load
-// costs its wave 40 to 70 cycles): the leaders, whose softmax phase is the
-// step's second half, all at its start, so that the loads have the whole phase
-// to arrive before the step ends; the others at the start (KG = 1) or spread
-// over the phase (KG > 1, where half as many scores go between two loads).
-// Issued unconditionally but in the last step: near the end of a row the
-// key-block indices repeat the last block and the loads land in slots no later
-// step reads.
+// The loads of one pipeline step: the next K tile and the next V tile.  A tile
+// load costs its wave 40 to 70 cycles (the four waves of a half step share the
+// CU's 64 bytes a cycle).  Whole tiles (KG = 1): every wave issues its share at the
+// start of its softmax phase, which has the slack; the leaders' is the step's
+// second half, so their loads have that phase to arrive before the step ends.
+// Split tiles (KG > 1): a step's computation is a half or a quarter, its loads are
+// the same, and what bounds it is their issue and arrival.  All waves issue
+// them in the step's first half, spread over the phase they are in: the
+// leaders' GEMM phase and the others' softmax phase.  In 64-row items, per
+// step: 1.23 us with the leaders' loads at the start of their softmax phase,
+// 1.16 this way (one head of 15,600 tokens: 149.7 and 141.9 us; 4,680 tokens:
+// 46.8 and 44.4; 128-row items, one head of 32,760 tokens token-exact: 447.6 and
+// 437.7; interleaved on one board).  Every wave's in its softmax phase with a
+// whole step to arrive, the key halves of leaders and others loaded apart, was
+// slower (1% to 8%): arrival alone is not the bound, bursts are.
+// Near the end of a row the key-block indices repeat the last block and the loads
+// land in slots no later step reads (in the last step the leaders of whole tiles
+// issue none).
 struct StepLoads {
   uint32_t k_dst, v_dst;                 // LDS tile addresses
   __amdgpu_buffer_rsrc_t rk, rv;         // resources starting at the tiles
@@ -536,12 +546,14 @@ __device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& s
 // step is two key blocks (two halves of the key groups), and `keep` says which
 // of them the wave's query block keeps; V of the other is left out, so that
 // what the keys of a key block hold that a query block does not keep (inf, NaN)
-// never reaches it.
+// never reaches it.  `sl` (null with SKIP): the step's tile loads, issued evenly
+// over the phase.
 template <int NU, int RSUM, bool SKIP>
 __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
                                            const bf16x8 (&qf)[4][2], Scores<NU>& sc,
                                            const Probs<NU>& pr, WaveState& st,
-                                           const FragAddr& fa, const bf16x8& ones, int keep) {
+                                           const FragAddr& fa, const bf16x8& ones, int keep,
+                                           const StepLoads* sl) {
   if constexpr (SKIP) {
     if (keep != 3) {
 #pragma unroll
@@ -591,9 +603,12 @@ __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
       }
   }
   // What MFMA m of the phase's 2 * NF carries along: the read of half a V
-  // fragment, or of a K fragment at every second one.
+  // fragment, or of a K fragment at every second one; a tile load at every
+  // EVERY-th.
+  constexpr int EVERY = 2 * NF / (2 * Tile::LOADS);
   i16x4 lo = i16x4{};
   auto carry = [&](int m) {
+    if (sl && m % EVERY == EVERY - 1) issue_step_load(*sl, m / EVERY);
     const int i = m / 2 + AHEAD;
     if (i < NF) {
       if (i >= NP) {
@@ -1138,7 +1153,8 @@ __device__ __forceinline__ void attn_tile(
       const char* const vj = v_lds + (j & 1) * TL::BYTES;          // V(j)
       // half-period 2j
       if (lead) {
-        gemm_phase<NU, RSUM, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep);
+        gemm_phase<NU, RSUM, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep,
+                                   KG == 1 ? nullptr : &sl);
         keep = mask_step(sc, w1, o1, false);
       } else {
         if constexpr (KG == 1) issue_step_loads(sl);
@@ -1148,11 +1164,11 @@ __device__ __forceinline__ void attn_tile(
       // half-period 2j+1
       if (lead) {
         if (j + 1 < n) {
-          issue_step_loads(sl);
+          if constexpr (KG == 1) issue_step_loads(sl);
           softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, nullptr);
         }
       } else {
-        gemm_phase<NU, RSUM, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep);
+        gemm_phase<NU, RSUM, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep, nullptr);
         keep = mask_step(sc, w1, o1, true);
       }
       wait_loads_and_sync();
@@ -1361,10 +1377,12 @@ int tiles_of(const AttnArgs& a, int kg) {
 // over the key groups of a workgroup (Split) gives more, shorter items: a
 // 128-row item takes 0.60 of a 256-row tile's time and a 64-row one 0.42 (not
 // 0.5 and 0.25: each K/V tile brought into LDS serves fewer rows; measured with
-// every CU busy, Wan-1.3B 1x and 6x: 4.50 and 29.2 ms whole, 5.44 and 34.1 ms in
-// 128-row items, 7.48 and 42.7 ms in 64-row items; with 64-token blocks 10.8
-// against 13.7 ms).  So whole tiles fill all rounds but the last one or two,
-// and what remains is split if that ends earlier.
+// every CU busy, Wan-1.3B 1x and 6x: 4.48 and 28.7 ms whole, 5.28 and 33.3 ms in
+// 128-row items, 7.69 and 43.1 ms in 64-row items; with 64-token blocks at 2x 9.34,
+// 10.6 and 13.7 ms; walks of 16 steps 0.72 and 0.48, of 4 steps 0.94 and 0.61,
+// where a tile's fixed times count: the plan they give is the same).  So whole
+// tiles fill all rounds but the last one or two, and what remains is split if
+// that ends earlier.
 // 64-token blocks split the same way; in the token-exact form, whose step words
 // hold two query blocks at most, 128-row tiles into 64-row ones.
 Plan make_plan(const AttnArgs& a, int block, AttnMode mode, int cus) {

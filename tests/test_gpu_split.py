@@ -90,6 +90,30 @@ def test_random_csr_by_plan(H, N, block):
 
 
 @pytest.mark.parametrize("block", [128, 64])
+@pytest.mark.parametrize("tiles", [2, 84])
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5])
+def test_short_walks_of_split_tiles(steps, tiles, block):
+    """64-row parts (few tiles) and 128-row parts whose walks are as short as
+    the pipeline of tile loads is deep, and one or two steps longer."""
+    N = 128 * steps - 5
+    H = max(1, tiles // -(-N // 256))
+    _say(f"[split] short walks H={H} N={N} B={block}")
+    q, k, v = make_qkv(H, N, seed=steps + tiles)
+    nb = -(-N // block)
+    rp, ci = _random_csr(nb, 7 * steps + block, set())
+    m = L.csr_mask(torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), N, block)
+    out = L.attention(q.cuda(), k.cuda(), v.cuda(), m)
+    dense = L.dense_attention(q.cuda(), k.cuda(), v.cuda(), block=block)
+    torch.cuda.synchronize()
+    heads = sorted({0, H - 1})
+    qs, ks, vs = (x[heads].float().numpy() for x in (q, k, v))
+    _check(out, OA.block_sparse_attention(qs, ks, vs, rp.tolist(), ci.tolist(), block), heads, N,
+           block)
+    frp, fci = [i * nb for i in range(nb + 1)], list(range(nb)) * nb
+    _check(dense, OA.block_sparse_attention(qs, ks, vs, frp, fci, block), heads, N, block)
+
+
+@pytest.mark.parametrize("block", [128, 64])
 @pytest.mark.parametrize("H,T,P,text", [(3, 5, 131, 0), (37, 9, 193, 3), (66, 8, 201, 60)])
 def test_exact_by_plan(H, T, P, text, block):
     _say(f"[split] exact form H={H} T={T} P={P} text={text} B={block}")
