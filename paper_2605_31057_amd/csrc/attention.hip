@@ -339,26 +339,27 @@ __device__ __forceinline__ void compute_scores(const char* lds_k, const bf16x8 (
   }
 }
 
-// Row sums l are kept one of two ways (RSUM): on the matrix core, as a
-// 16x16 MFMA accumulator that the GEMM phase adds each step's bf16 P into
-// (register 0 of every lane holds its row's sum), or on the VALU, as a
-// partial sum per lane and query tile of the fp32 probabilities of the lane's
-// own keys that the softmax phase adds into (the four lanes of a row hold
-// its parts).  Whole tiles use the matrix core: 8 MFMAs instead of 64 adds in
-// the softmax phase, whose VALU slots are the scarcer (1.2-1.4% at Wan 6x and
-// 1x, interleaved).  It sums exactly the P that multiplies V, so the weights
-// of a row add up to 1, and the result is no further from float64 than with
-// fp32 sums: 2-norm of the error relative to
-// the result, dense attention over 4,680 keys of N(0, 1) with Q and K times 1,
-// 2, 4, 8: 2.34e-3, 2.07e-3, 1.75e-3 and 1.07e-3 with fp32 sums, 2.34e-3,
-// 1.87e-3, 1.53e-3 and 0.94e-3 with these.
-enum RowSums { RSUM_MFMA = 0, RSUM_VALU = 1 };
-
+// Row sums l are taken on the matrix core, as a 16x16 MFMA accumulator that the
+// GEMM phase adds each step's bf16 P into (register 0 of every lane holds its
+// row's sum): 8 MFMAs a step instead of 64 adds in the softmax phase, whose VALU
+// slots are the scarcer (fp32 sums on the VALU: Wan-1.3B 6x step 29.7 ms against
+// 28.5; split tiles 3% slower, one head of 32,760 tokens 437 us against 419).
+// They sum exactly the P that multiplies V, so the weights of a row add up to 1
+// and P's rounding largely cancels: with d_i the relative rounding of p_i the
+// result is off by sum d_i p_i (v_i - o) / l instead of sum d_i p_i v_i / l.
+// Measured, 2-norm of the error against float64 relative to the result, fp32 sums
+// (against the running maximum) and these: 22 shapes of N(0, 1) inputs in all
+// forms 2.29e-3 to 2.36e-3 and 2.25e-3 to 2.36e-3, not larger in any but one (an
+// exact one of 4 heads by 0.1%, in split tiles while those summed on the VALU);
+// one head of 4,680 tokens, split, with
+// Q and K times 1, 2, 4, 8, 16 2.36e-3, 2.07e-3, 1.77e-3, 1.07e-3, 0.56e-3 and
+// 2.36e-3, 1.82e-3, 1.51e-3, 0.93e-3, 0.49e-3, and 12 heads of 5,460, whole,
+// 2.33e-3, 2.06e-3, 1.75e-3, 1.07e-3, 0.56e-3 and 2.33e-3, 1.88e-3, 1.54e-3,
+// 0.94e-3, 0.49e-3.
 struct WaveState {
   f32x4 o[8][2];   // O^T tiles [d tile][query tile]: d = 16*dt + C row
   float m[2];      // reference of the exponentials (log2 domain), the same in a row's four lanes
-  f32x4 lt[2];     // RSUM_MFMA: row sums
-  float l[2];      // RSUM_VALU: partial row sums of the lane's keys
+  f32x4 l[2];      // row sums
   int ready;       // every row has a finite m
 };
 
@@ -433,7 +434,7 @@ struct Probs {
 
 // Raises the reference m of every row whose largest score of the step lies
 // above it, to HEADROOM above that score, and rescales the row's O and l.
-template <int NU, int RSUM>
+template <int NU>
 __device__ __forceinline__ void raise_max(const Scores<NU>& sc, WaveState& st,
                                           float scale_log2) {
   float mx[2];
@@ -453,8 +454,7 @@ __device__ __forceinline__ void raise_max(const Scores<NU>& sc, WaveState& st,
     const float m = raise ? top + HEADROOM : st.m[qt];
     const float a = raise ? __builtin_amdgcn_exp2f(st.m[qt] - m) : 1.f;
     st.m[qt] = m;
-    if constexpr (RSUM == RSUM_MFMA) st.lt[qt][0] *= a;
-    else st.l[qt] *= a;
+    st.l[qt][0] *= a;
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) st.o[dt][qt] *= a;
   }
@@ -462,15 +462,15 @@ __device__ __forceinline__ void raise_max(const Scores<NU>& sc, WaveState& st,
                                          st.m[1] == -__builtin_inff()) == 0;
 }
 
-// P = 2^(s*scale - m) in bf16 from one step's scores, l += its row sums
-// (RSUM_VALU), with the tile loads in `sl` (may be null) issued along the way.
+// P = 2^(s*scale - m) in bf16 from one step's scores, with the tile loads in `sl`
+// (may be null) issued along the way.
 // Returns the bits of all probabilities or-ed together.  Scheduling barriers
 // every 8 scores keep the compiler from hoisting many exponentials at once
 // (S, P, O and Q already fill the register file).
-template <int NU, int RSUM>
+template <int NU>
 __device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU>& pr,
-                                                  float (&l)[2], const float (&m)[2],
-                                                  float scale_log2, const StepLoads* sl) {
+                                                  const float (&m)[2], float scale_log2,
+                                                  const StepLoads* sl) {
   constexpr int NLOADS = 2 * Tile::LOADS;
   constexpr int GROUPS = 4 * NU;                     // groups of 4 scores
   constexpr int PER = (NLOADS + GROUPS - 1) / GROUPS;
@@ -493,7 +493,6 @@ __device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU
               __builtin_fmaf(sc.s[2 * u + t][qt][r], scale_log2, -m[qt]));
           const float b = __builtin_amdgcn_exp2f(
               __builtin_fmaf(sc.s[2 * u + t][qt][r + 1], scale_log2, -m[qt]));
-          if constexpr (RSUM == RSUM_VALU) l[qt] += a + b;
           const bf16x2 pk = {(__bf16)a, (__bf16)b};
           bits |= __builtin_bit_cast(uint32_t, pk);
           pr.p[u][qt][4 * t + r] = pk[0];
@@ -515,31 +514,24 @@ __device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU
 // four scores instead of one max3 per two and the exchange between a row's
 // lanes.  The result is exact either way because O and l always use the same
 // m.  Until every row has an m (st.ready), m is raised first.
-template <int NU, int RSUM>
+template <int NU>
 __device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& st,
                                               Probs<NU>& pr, float scale_log2,
                                               const StepLoads* sl) {
   const bool first = !__builtin_amdgcn_readfirstlane(st.ready);
-  if (first) raise_max<NU, RSUM>(sc, st, scale_log2);
-  float l[2] = {st.l[0], st.l[1]};
+  if (first) raise_max<NU>(sc, st, scale_log2);
   float m[2];
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt) m[qt] = st.m[qt] == -__builtin_inff() ? 0.f : st.m[qt];
-  const uint32_t bits = probabilities<NU, RSUM>(sc, pr, l, m, scale_log2, sl);
+  const uint32_t bits = probabilities<NU>(sc, pr, m, scale_log2, sl);
   if (__builtin_amdgcn_ballot_w64((bits & 0x40004000u) != 0u) && !first) {
-    raise_max<NU, RSUM>(sc, st, scale_log2);
-    l[0] = st.l[0];
-    l[1] = st.l[1];
-    m[0] = st.m[0];
-    m[1] = st.m[1];
-    probabilities<NU, RSUM>(sc, pr, l, m, scale_log2, nullptr);
+    raise_max<NU>(sc, st, scale_log2);
+    probabilities<NU>(sc, pr, st.m, scale_log2, nullptr);
   }
-  st.l[0] = l[0];
-  st.l[1] = l[1];
 }
 
-// GEMM phase of the ping-pong schedule: with RSUM_MFMA, l += the row sums of
-// P(j) (one MFMA per 32 keys and query tile, `ones` its A operand); then
+// GEMM phase of the ping-pong schedule: l += the row sums of P(j) (one MFMA per
+// 32 keys and query tile, `ones` its A operand); then
 // O += P(j) V(j) and S(j+1) = K(j+1) Q^T into `sc`, with K and V fragments
 // read AHEAD fragments early.  The row-sum MFMAs come first: their operands are already in
 // registers, so they run while the first fragments arrive from LDS.  SKIP: the
@@ -548,7 +540,7 @@ __device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& s
 // what the keys of a key block hold that a query block does not keep (inf, NaN)
 // never reaches it.  `sl` (null with SKIP): the step's tile loads, issued evenly
 // over the phase.
-template <int NU, int RSUM, bool SKIP>
+template <int NU, bool SKIP>
 __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
                                            const bf16x8 (&qf)[4][2], Scores<NU>& sc,
                                            const Probs<NU>& pr, WaveState& st,
@@ -561,8 +553,8 @@ __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
         if (!((keep >> (u / (NU / 2))) & 1)) continue;
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt) {
-          st.lt[qt] =
-              __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pr.p[u][qt], st.lt[qt], 0, 0, 0);
+          st.l[qt] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pr.p[u][qt], st.l[qt], 0, 0, 0);
         }
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) {
@@ -592,16 +584,13 @@ __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
 #pragma unroll
   for (int i = 0; i < AHEAD; ++i) fr[i] = frag(i);
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (RSUM == RSUM_MFMA) {
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt)
+  for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        st.lt[qt] =
-            __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pr.p[u][qt], st.lt[qt], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-  }
+    for (int u = 0; u < NU; ++u) {
+      st.l[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pr.p[u][qt], st.l[qt], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   // What MFMA m of the phase's 2 * NF carries along: the read of half a V
   // fragment, or of a K fragment at every second one; a tile load at every
   // EVERY-th.
@@ -1082,11 +1071,9 @@ __device__ __forceinline__ void attn_tile(
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) ws.o[dt][qt] = f32x4{};
     ws.m[qt] = -__builtin_inff();
-    ws.lt[qt] = f32x4{};
-    ws.l[qt] = 0.f;
+    ws.l[qt] = f32x4{};
   }
   ws.ready = 0;
-  constexpr int RSUM = KG > 1 ? RSUM_VALU : RSUM_MFMA;
   // A operand of the row-sum MFMA: rows 0, 4, 8 and 12 (register 0 of every
   // lane of the result) take all 32 keys, the others none.
   bf16x8 ones;
@@ -1136,7 +1123,7 @@ __device__ __forceinline__ void attn_tile(
     compute_scores<NU>(k_lds, qf, sc, fa);   // S(0)
     int keep = mask_step(sc, w0, o0, upper);
     Probs<NU> pr;
-    if (lead) softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, nullptr);   // P(0)
+    if (lead) softmax_phase<NU>(sc, ws, pr, scale_log2, nullptr);   // P(0)
     __syncthreads();
     for (int j = 0; j < n; ++j) {
       // Word of step j+3 from the walk's LDS, read now and used at the end of
@@ -1153,22 +1140,22 @@ __device__ __forceinline__ void attn_tile(
       const char* const vj = v_lds + (j & 1) * TL::BYTES;          // V(j)
       // half-period 2j
       if (lead) {
-        gemm_phase<NU, RSUM, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep,
+        gemm_phase<NU, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep,
                                    KG == 1 ? nullptr : &sl);
         keep = mask_step(sc, w1, o1, false);
       } else {
         if constexpr (KG == 1) issue_step_loads(sl);
-        softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, KG == 1 ? nullptr : &sl);
+        softmax_phase<NU>(sc, ws, pr, scale_log2, KG == 1 ? nullptr : &sl);
       }
       __syncthreads();
       // half-period 2j+1
       if (lead) {
         if (j + 1 < n) {
           if constexpr (KG == 1) issue_step_loads(sl);
-          softmax_phase<NU, RSUM>(sc, ws, pr, scale_log2, nullptr);
+          softmax_phase<NU>(sc, ws, pr, scale_log2, nullptr);
         }
       } else {
-        gemm_phase<NU, RSUM, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep, nullptr);
+        gemm_phase<NU, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep, nullptr);
         keep = mask_step(sc, w1, o1, true);
       }
       wait_loads_and_sync();
@@ -1183,18 +1170,7 @@ __device__ __forceinline__ void attn_tile(
     __syncthreads();
   }
 
-  // Row sums: whole in every lane (RSUM_MFMA), or a part in each of a row's
-  // four lanes.
-  float lsum[2];
-#pragma unroll
-  for (int qt = 0; qt < 2; ++qt) {
-    if constexpr (RSUM == RSUM_MFMA) {
-      lsum[qt] = ws.lt[qt][0];
-    } else {
-      const float l2 = ws.l[qt] + __shfl_xor(ws.l[qt], 16);
-      lsum[qt] = l2 + __shfl_xor(l2, 32);
-    }
-  }
+  const float lsum[2] = {ws.l[0][0], ws.l[1][0]};   // whole in every lane
   if constexpr (KG > 1) {
     combine_groups<KG>(lds, ws, lsum, oh, o_st, qrow, N, wave, lane);
   } else {

@@ -140,6 +140,33 @@ def test_exact_by_plan(H, T, P, text, block):
     assert_close(worst, total / count)
 
 
+@pytest.mark.parametrize("block", [128, 64])
+@pytest.mark.parametrize("H,N", SHAPES)
+def test_weights_add_up_to_one(H, N, block):
+    """The same V row at every token comes back bit for bit from every kind of
+    tile: the row sums are those of the bf16 probabilities that multiply V, so
+    only the fp32 accumulation (relative error below N * 2^-24 <= 2^-12) and the
+    exact value's rounding to itself stand between.  Wide logits, whose
+    probabilities fall anywhere between two bf16 values."""
+    _say(f"[split] constant V H={H} N={N} B={block}")
+    q, k, _ = make_qkv(H, N, seed=H + N)
+    row = torch.randn(128, generator=torch.Generator().manual_seed(H)).to(torch.bfloat16)
+    qd, kd, vd = (q * 4).cuda(), k.cuda(), row.expand(H, N, 128).contiguous().cuda()
+    nb = -(-N // block)
+    rp, ci = _random_csr(nb, H + block, set())
+    m = L.csr_mask(torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), N, block)
+    outs = [L.attention(qd, kd, vd, m), L.dense_attention(qd, kd, vd, block=block)]
+    P = max(N // 3, block)
+    if N > P:
+        csr = L.build_mask(N // P, P, block, 0, L.Params(window=0, tper=3, text_tokens=N % P),
+                           exact=True)
+        csr.upload()
+        outs.append(L.attention_exact(qd, kd, vd, csr.exact_mask()))
+    torch.cuda.synchronize()
+    for out in outs:
+        assert torch.equal(out, vd)
+
+
 @pytest.mark.parametrize("peak", [0.0, 400.0])
 def test_reference_is_raised_within_a_walk(peak):
     """Scores that grow along the walk (the walk goes from the last key block
