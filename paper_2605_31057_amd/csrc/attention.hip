@@ -102,7 +102,10 @@ typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int D = 128;             // head_dim
+// Distance (log2) of a row's reference above the largest score it was set from,
+// before and after the wave's first redo of a step (softmax_phase).
 constexpr float HEADROOM = 7.f;
+constexpr float WIDE_HEADROOM = 39.f;
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
@@ -356,11 +359,12 @@ __device__ __forceinline__ void compute_scores(const char* lds_k, const bf16x8 (
 // 2.36e-3, 1.82e-3, 1.51e-3, 0.93e-3, 0.49e-3, and 12 heads of 5,460, whole,
 // 2.33e-3, 2.06e-3, 1.75e-3, 1.07e-3, 0.56e-3 and 2.33e-3, 1.88e-3, 1.54e-3,
 // 0.94e-3, 0.49e-3.
+constexpr int READY = 1, WIDE = 2;
 struct WaveState {
   f32x4 o[8][2];   // O^T tiles [d tile][query tile]: d = 16*dt + C row
   float m[2];      // reference of the exponentials (log2 domain), the same in a row's four lanes
   f32x4 l[2];      // row sums
-  int ready;       // every row has a finite m
+  int flags;       // READY: every row has a finite m; WIDE: a step was redone
 };
 
 // Keys at or past N (ragged last block) do not exist: their scores become
@@ -433,10 +437,11 @@ struct Probs {
 };
 
 // Raises the reference m of every row whose largest score of the step lies
-// above it, to HEADROOM above that score, and rescales the row's O and l.
+// above it, to `head` above that score, the others by `lift`, and rescales the rows'
+// O and l.
 template <int NU>
 __device__ __forceinline__ void raise_max(const Scores<NU>& sc, WaveState& st,
-                                          float scale_log2) {
+                                          float scale_log2, float head, float lift) {
   float mx[2];
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt) {
@@ -450,16 +455,16 @@ __device__ __forceinline__ void raise_max(const Scores<NU>& sc, WaveState& st,
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt) {
     const float top = mx[qt] * scale_log2;
-    const bool raise = top > st.m[qt];
-    const float m = raise ? top + HEADROOM : st.m[qt];
-    const float a = raise ? __builtin_amdgcn_exp2f(st.m[qt] - m) : 1.f;
+    const float m = top > st.m[qt] ? top + head : st.m[qt] + lift;
+    const float a = m == st.m[qt] ? 1.f : __builtin_amdgcn_exp2f(st.m[qt] - m);
     st.m[qt] = m;
     st.l[qt][0] *= a;
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) st.o[dt][qt] *= a;
   }
-  st.ready = __builtin_amdgcn_ballot_w64(st.m[0] == -__builtin_inff() ||
-                                         st.m[1] == -__builtin_inff()) == 0;
+  const bool ready = __builtin_amdgcn_ballot_w64(st.m[0] == -__builtin_inff() ||
+                                                 st.m[1] == -__builtin_inff()) == 0;
+  st.flags = (st.flags & WIDE) | (ready ? READY : 0);
 }
 
 // P = 2^(s*scale - m) in bf16 from one step's scores, with the tile loads in `sl`
@@ -506,26 +511,40 @@ __device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU
 
 // Softmax phase of the ping-pong schedule: block j's scores (in `sc`) become
 // its probabilities P (bf16, in `pr`), against the rows' reference m as it
-// stands.  m is HEADROOM above the largest score it was set from, so p stays
-// far below 2 until a score exceeds that one by HEADROOM + 1; then some p
+// stands.  m is some headroom above the largest score it was set from, so p stays
+// far below 2 until a score exceeds that one by the headroom + 1; then some p
 // (rounded to bf16) is at least 2, which sets the top exponent bit of its half
 // of the word (inf and NaN do too), and the wave raises m and does the step's
 // probabilities again.  So a step usually takes no row maximum: one or3 per
 // four scores instead of one max3 per two and the exchange between a row's
 // lanes.  The result is exact either way because O and l always use the same
-// m.  Until every row has an m (st.ready), m is raised first.
+// m.  Until every row has an m (READY), m is raised first.
+//
+// The headroom is 7 at first: products p v then keep their bits for v down to
+// 2^-130.  Logits so wide that a step is redone would cross it again and again
+// (one redoing wave holds up the other seven at the half step's barrier), so the
+// wave's first redo takes 39 from then on, for v down to 2^-100.  Wan-1.3B 6x
+// step with Q and K times 1, 2, 4, 8, ms, interleaved on one board: 27.8, 29.9, 31.0
+// and 30.0 with 7 throughout, 27.7, 28.5, 28.6 and 28.5 so (with a row maximum every
+// step and 32x32x16 MFMAs 30.4, 31.8, 32.0 and 28.9).  Times 16 and more, where one
+// key holds all of a row's weight, it is 3 to 8% slower than a row maximum every
+// step; taking one first after 8 to 32 redos mended that, but cost 3 to 5% at times
+// 8, or a spilled register everywhere where the rescale was made conditional.
 template <int NU>
 __device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& st,
                                               Probs<NU>& pr, float scale_log2,
                                               const StepLoads* sl) {
-  const bool first = !__builtin_amdgcn_readfirstlane(st.ready);
-  if (first) raise_max<NU>(sc, st, scale_log2);
+  const int flags = __builtin_amdgcn_readfirstlane(st.flags);
+  const bool first = !(flags & READY);
+  if (first) raise_max<NU>(sc, st, scale_log2, (flags & WIDE) ? WIDE_HEADROOM : HEADROOM, 0.f);
   float m[2];
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt) m[qt] = st.m[qt] == -__builtin_inff() ? 0.f : st.m[qt];
   const uint32_t bits = probabilities<NU>(sc, pr, m, scale_log2, sl);
   if (__builtin_amdgcn_ballot_w64((bits & 0x40004000u) != 0u) && !first) {
-    raise_max<NU>(sc, st, scale_log2);
+    st.flags |= WIDE;
+    raise_max<NU>(sc, st, scale_log2, WIDE_HEADROOM,
+                  (flags & WIDE) ? 0.f : WIDE_HEADROOM - HEADROOM);
     probabilities<NU>(sc, pr, st.m, scale_log2, nullptr);
   }
 }
@@ -1073,7 +1092,7 @@ __device__ __forceinline__ void attn_tile(
     ws.m[qt] = -__builtin_inff();
     ws.l[qt] = f32x4{};
   }
-  ws.ready = 0;
+  ws.flags = 0;
   // A operand of the row-sum MFMA: rows 0, 4, 8 and 12 (register 0 of every
   // lane of the result) take all 32 keys, the others none.
   bf16x8 ones;

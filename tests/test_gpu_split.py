@@ -185,6 +185,53 @@ def test_reference_is_raised_within_a_walk(peak):
     _check(out, ref, list(range(H)), N, 128)
 
 
+@pytest.mark.parametrize("v_exp", [0, -90])
+@pytest.mark.parametrize("form,block", [("dense", 128), ("block", 128), ("block", 64),
+                                        ("exact", 128), ("exact", 64)])
+def test_reference_is_raised_in_whole_tiles(form, block, v_exp):
+    """The same in launches of whole tiles (256 of 256 rows; token-exact with
+    64-token blocks 512 of 128): rows whose reference rises by more than either
+    headroom, step after step, beside rows that never raise it; V down to
+    2^-90, whose products with the smallest references still are normal
+    numbers."""
+    H, P, T = 64, 333, 3
+    N = P * T + 1
+    _say(f"[split] raised reference, whole tiles, {form} B={block} V*2^{v_exp}")
+    q, k, v = make_qkv(H, N, seed=4)
+    q[:, 1::3] *= 0.02
+    k *= torch.linspace(30.0, 0.1, N).view(1, N, 1).to(torch.bfloat16)
+    k[:, 7] = (q[:, 702] * 3).to(torch.bfloat16)
+    vd = (v.float() * 2.0 ** v_exp).to(torch.bfloat16).cuda()
+    heads, nb = [0, H - 1], -(-N // block)
+    qs, ks, vs = (x[heads].float().numpy() for x in (q, k, v))
+    if form == "exact":
+        p = L.Params(window=0, tper=3, text_tokens=1)
+        csr = L.build_mask(T, P, block, 0, p, exact=True)
+        csr.upload()
+        out = L.attention_exact(q.cuda(), k.cuda(), vd, csr.exact_mask())
+        _, _, A = M.attended_frames(T, 0, W=0, tper=3)
+        seg = np.minimum(np.arange(N) // P, T)
+        att = np.ones((T + 1, T + 1), dtype=bool)
+        for t in range(T):
+            att[t, :T] = [u in A[t] for u in range(T)]
+        s = np.where(att[seg][:, seg], qs @ ks.transpose(0, 2, 1) / np.sqrt(128.0), -np.inf)
+        pr = np.exp(s - s.max(-1, keepdims=True))
+        full = (pr / pr.sum(-1, keepdims=True)) @ vs
+        ref = {(h, qb): full[h, qb * block:(qb + 1) * block] for h in range(2) for qb in range(nb)}
+    else:
+        if form == "block":
+            rp, ci = _random_csr(nb, block, set())
+            m = L.csr_mask(torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), N, block)
+            out = L.attention(q.cuda(), k.cuda(), vd, m)
+            rp, ci = rp.tolist(), ci.tolist()
+        else:
+            rp, ci = [i * nb for i in range(nb + 1)], list(range(nb)) * nb
+            out = L.dense_attention(q.cuda(), k.cuda(), vd, block=block)
+        ref = OA.block_sparse_attention(qs, ks, vs, rp, ci, block)
+    torch.cuda.synchronize()
+    _check(out.float() * 2.0 ** -v_exp, ref, heads, N, block)
+
+
 def test_unkept_key_blocks_do_not_reach_a_query_block():
     """Four 64-token query blocks share a tile; V of a key block that only the
     first of them keeps may hold anything."""
