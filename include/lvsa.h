@@ -321,7 +321,8 @@ typedef struct lvsa_tensor {
  * head_dim = 128; mask->block is 64 or 128 and mask->n_q_blocks =
  * mask->n_kv_blocks = ceil(N / B) <= 8000 (a workgroup merges the CSR rows of
  * its tile's query blocks in LDS).  Rows i >= N of `out` are never written;
- * a query block whose row is empty gets zeros.  out must not overlap q, k or
+ * a query block whose row is empty gets zeros, and key blocks that its row does
+ * not hold never reach it, whatever their K and V hold.  out must not overlap q, k or
  * v.  The result is deterministic: for given heads, tokens and block, the keys
  * of a row are taken in a fixed order, whichever workgroup computes it.
  * Errors: EINVAL (nulls, shape mismatch), EUNSUPPORTED (head_dim, block,

@@ -12,7 +12,7 @@
 //   Adjacent query blocks mostly keep the same key blocks (they touch the same
 //   frames), so each K/V tile brought from HBM/L2 into LDS serves 256 query
 //   rows; a key block that only some of the query blocks keep is masked out
-//   (no valid keys) for the waves of the others.
+//   (no valid keys, V left out of the products) for the waves of the others.
 //   Where whole tiles leave compute units idle (few tiles, or a last round that
 //   is nearly empty), tiles are split over the key groups of a workgroup
 //   (Split): 128 or 64 rows, the eight waves sharing the step's keys as well as
@@ -252,16 +252,15 @@ __device__ __forceinline__ void issue_tile(uint32_t lds, __amdgpu_buffer_rsrc_t 
 struct StepLoads {
   uint32_t k_dst, v_dst;                 // LDS tile addresses
   __amdgpu_buffer_rsrc_t rk, rv;         // resources starting at the tiles
-  const LoadPlan* kp;
-  const LoadPlan* vp;
+  LoadPlan kp, vp;
 };
 
 __device__ __forceinline__ void issue_step_load(const StepLoads& sl, int i) {
   if (i < Tile::LOADS)
-    issue_load(sl.k_dst + sl.kp->lds_w + 1024u * Tile::NW * i, sl.rk, sl.kp->lane_off, 64u * i);
+    issue_load(sl.k_dst + sl.kp.lds_w + 1024u * Tile::NW * i, sl.rk, sl.kp.lane_off, 64u * i);
   else
-    issue_load(sl.v_dst + sl.vp->lds_w + 1024u * Tile::NW * (i - Tile::LOADS), sl.rv,
-               sl.vp->lane_off, 64u * (i - Tile::LOADS));
+    issue_load(sl.v_dst + sl.vp.lds_w + 1024u * Tile::NW * (i - Tile::LOADS), sl.rv,
+               sl.vp.lane_off, 64u * (i - Tile::LOADS));
 }
 
 __device__ __forceinline__ void issue_step_loads(const StepLoads& sl) {
@@ -468,14 +467,14 @@ __device__ __forceinline__ void raise_max(const Scores<NU>& sc, WaveState& st,
 }
 
 // P = 2^(s*scale - m) in bf16 from one step's scores, with the tile loads in `sl`
-// (may be null) issued along the way.
+// issued along the way (LOADS).
 // Returns the bits of all probabilities or-ed together.  Scheduling barriers
 // every 8 scores keep the compiler from hoisting many exponentials at once
 // (S, P, O and Q already fill the register file).
-template <int NU>
+template <int NU, bool LOADS>
 __device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU>& pr,
                                                   const float (&m)[2], float scale_log2,
-                                                  const StepLoads* sl) {
+                                                  const StepLoads& sl) {
   constexpr int NLOADS = 2 * Tile::LOADS;
   constexpr int GROUPS = 4 * NU;                     // groups of 4 scores
   constexpr int PER = (NLOADS + GROUPS - 1) / GROUPS;
@@ -490,8 +489,8 @@ __device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU
       for (int t = 0; t < 2; ++t) {
         const int grp = 4 * u + 2 * qt + t;
         if (t == 0) __builtin_amdgcn_sched_barrier(0);
-        if (sl && grp % EVERY == 0)
-          for (int i = 0; i < PER && issued < NLOADS; ++i) issue_step_load(*sl, issued++);
+        if (LOADS && grp % EVERY == 0)
+          for (int i = 0; i < PER && issued < NLOADS; ++i) issue_step_load(sl, issued++);
 #pragma unroll
         for (int r = 0; r < 4; r += 2) {
           const float a = __builtin_amdgcn_exp2f(
@@ -504,8 +503,8 @@ __device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU
           pr.p[u][qt][4 * t + r + 1] = pk[1];
         }
       }
-  if (sl)
-    for (; issued < NLOADS; ++issued) issue_step_load(*sl, issued);
+  if (LOADS)
+    for (; issued < NLOADS; ++issued) issue_step_load(sl, issued);
   return bits;
 }
 
@@ -530,22 +529,22 @@ __device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU
 // key holds all of a row's weight, it is 3 to 8% slower than a row maximum every
 // step; taking one first after 8 to 32 redos mended that, but cost 3 to 5% at times
 // 8, or a spilled register everywhere where the rescale was made conditional.
-template <int NU>
+template <int NU, bool LOADS>
 __device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& st,
                                               Probs<NU>& pr, float scale_log2,
-                                              const StepLoads* sl) {
+                                              const StepLoads& sl) {
   const int flags = __builtin_amdgcn_readfirstlane(st.flags);
   const bool first = !(flags & READY);
   if (first) raise_max<NU>(sc, st, scale_log2, (flags & WIDE) ? WIDE_HEADROOM : HEADROOM, 0.f);
   float m[2];
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt) m[qt] = st.m[qt] == -__builtin_inff() ? 0.f : st.m[qt];
-  const uint32_t bits = probabilities<NU>(sc, pr, m, scale_log2, sl);
+  const uint32_t bits = probabilities<NU, LOADS>(sc, pr, m, scale_log2, sl);
   if (__builtin_amdgcn_ballot_w64((bits & 0x40004000u) != 0u) && !first) {
     st.flags |= WIDE;
     raise_max<NU>(sc, st, scale_log2, WIDE_HEADROOM,
                   (flags & WIDE) ? 0.f : WIDE_HEADROOM - HEADROOM);
-    probabilities<NU>(sc, pr, st.m, scale_log2, nullptr);
+    probabilities<NU, false>(sc, pr, st.m, scale_log2, sl);
   }
 }
 
@@ -553,35 +552,38 @@ __device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& s
 // 32 keys and query tile, `ones` its A operand); then
 // O += P(j) V(j) and S(j+1) = K(j+1) Q^T into `sc`, with K and V fragments
 // read AHEAD fragments early.  The row-sum MFMAs come first: their operands are already in
-// registers, so they run while the first fragments arrive from LDS.  SKIP: the
-// step is two key blocks (two halves of the key groups), and `keep` says which
-// of them the wave's query block keeps; V of the other is left out, so that
-// what the keys of a key block hold that a query block does not keep (inf, NaN)
-// never reaches it.  `sl` (null with SKIP): the step's tile loads, issued evenly
-// over the phase.
-template <int NU, bool SKIP>
+// registers, so they run while the first fragments arrive from LDS.  LOADS: the
+// step's tile loads `sl` are issued evenly over the phase.
+//
+// SUBS: the key blocks of a step (halves of the wave's key groups) that the wave's
+// query block may or may not keep (0: it keeps all it walks); bit i of `keep` says
+// whether it keeps key block i.  V of the others is left out, so that what a key
+// block holds (inf, NaN) never reaches a query block that does not keep it; such a
+// step issues none of the loads.
+template <int NU, int SUBS, bool LOADS>
 __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
                                            const bf16x8 (&qf)[4][2], Scores<NU>& sc,
                                            const Probs<NU>& pr, WaveState& st,
                                            const FragAddr& fa, const bf16x8& ones, int keep,
-                                           const StepLoads* sl) {
-  if constexpr (SKIP) {
-    if (keep != 3) {
+                                           const StepLoads& sl) {
+  if constexpr (SUBS > 0) {
+    if (keep != (1 << SUBS) - 1) {
+      if constexpr (SUBS > 1) {
 #pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        if (!((keep >> (u / (NU / 2))) & 1)) continue;
-#pragma unroll
-        for (int qt = 0; qt < 2; ++qt) {
-          st.l[qt] =
-              __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pr.p[u][qt], st.l[qt], 0, 0, 0);
-        }
-#pragma unroll
-        for (int dt = 0; dt < 8; ++dt) {
-          const bf16x8 f = v_frag(lds_v, fa, dt, u);
+        for (int u = 0; u < NU; ++u) {
+          if (!((keep >> (u / (NU / SUBS))) & 1)) continue;
 #pragma unroll
           for (int qt = 0; qt < 2; ++qt)
-            st.o[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, pr.p[u][qt], st.o[dt][qt],
-                                                                   0, 0, 0);
+            st.l[qt] =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pr.p[u][qt], st.l[qt], 0, 0, 0);
+#pragma unroll
+          for (int dt = 0; dt < 8; ++dt) {
+            const bf16x8 f = v_frag(lds_v, fa, dt, u);
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt)
+              st.o[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, pr.p[u][qt],
+                                                                     st.o[dt][qt], 0, 0, 0);
+          }
         }
       }
       compute_scores<NU>(lds_k, qf, sc, fa);
@@ -616,7 +618,7 @@ __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
   constexpr int EVERY = 2 * NF / (2 * Tile::LOADS);
   i16x4 lo = i16x4{};
   auto carry = [&](int m) {
-    if (sl && m % EVERY == EVERY - 1) issue_step_load(*sl, m / EVERY);
+    if (LOADS && m % EVERY == EVERY - 1) issue_step_load(sl, m / EVERY);
     const int i = m / 2 + AHEAD;
     if (i < NF) {
       if (i >= NP) {
@@ -927,7 +929,7 @@ __device__ __forceinline__ void combine_groups(char* xch, WaveState& st, const f
 // ATTN_EXACT (CSR rows of token-exact entry words).
 // One tile: rows row0 .. row0 + ROWS - 1 of head `head`, using the
 // workgroup's LDS stages `lds` (K slots 0-1, V slots 0-1).  The tile lies in
-// one query block or covers two whole ones (2p and 2p + 1).
+// one query block or covers two or four whole ones.
 template <int BLOCK, int MODE, int KG>
 __device__ __forceinline__ void attn_tile(
     char* lds, WalkLds& walk, int head, int row0, const __bf16* __restrict__ qg,
@@ -943,6 +945,9 @@ __device__ __forceinline__ void attn_tile(
   constexpr bool QUAD = SP::ROWS == 4 * BLOCK;   // four query blocks
   constexpr bool PAIR = SP::ROWS == 2 * BLOCK;   // two of them, else (part of) one
   constexpr int SUBS = TL::KEYS / BLOCK;         // key blocks per step
+  // Key blocks of a step that a wave's query block may not keep (gemm_phase): of a
+  // tile in one query block none, of a wave whose keys lie in one key block one.
+  constexpr int SKIP = !SPARSE ? 0 : QUAD ? 2 : PAIR ? 1 : 0;
   // Four query blocks only in the block form: four 4-bit patterns and a key
   // block do not fit the token-exact form's words.
   static_assert(QUAD ? MODE == ATTN_BLOCK && SUBS == 2 : SP::ROWS <= 2 * BLOCK, "tile rows");
@@ -1007,15 +1012,20 @@ __device__ __forceinline__ void attn_tile(
   // Masks the scores of the key block of step word w for this wave's query
   // block: a key block that block does not keep has no valid keys.
   // `second`: the wave holds rows of query block 2p + 1.
-  auto mask_block = [&](Scores<NU>& sc, uint32_t w, bool second) {
+  // Returns whether the query block keeps it.
+  auto mask_block = [&](Scores<NU>& sc, uint32_t w, bool second) -> int {
     const int kb = kb_of(w);
     const uint32_t kept_bit = second ? 31u : 30u;      // block form
     const uint32_t pat_shift = second ? 28u : 24u;     // exact form
-    if constexpr (EXACT)
-      mask_exact<BLOCK, NU>(sc, (w >> pat_shift) & 0xFu, (int)((w >> 16) & 0xFFu),
-                             N - kb * BLOCK, sec_from, koff);
-    else
-      mask_tail<NU>(sc, lane, ((w >> kept_bit) & 1u) ? N - kb * BLOCK - koff : 0);
+    if constexpr (EXACT) {
+      const uint32_t pat = (w >> pat_shift) & 0xFu;
+      mask_exact<BLOCK, NU>(sc, pat, (int)((w >> 16) & 0xFFu), N - kb * BLOCK, sec_from, koff);
+      return pat != 0u;
+    } else {
+      const int kept = (int)((w >> kept_bit) & 1u);
+      mask_tail<NU>(sc, lane, kept ? N - kb * BLOCK - koff : 0);
+      return kept;
+    }
   };
 
   // The walk (sparse modes) or the key blocks nb-1 .. 0 (dense): n steps.
@@ -1114,7 +1124,8 @@ __device__ __forceinline__ void attn_tile(
     // half-periods 2j and 2j+1; K(j+2) and V(j+1) are issued in half-period 2j
     // (into the slots of K(j) and V(j-1), free since half-period 2j-1) and
     // waited for at the end of 2j+1.
-    // (With KG = 1 the followers are the waves of query block 2p + 1.)
+    // (With KG = 1 the followers are the waves of the tile's second half: its second
+    // query block, or the last two of four.)
     int lead_v = upper ? 0 : 1;
     asm("" : "+v"(lead_v));
     const bool lead = lead_v != 0;
@@ -1130,8 +1141,7 @@ __device__ __forceinline__ void attn_tile(
         mask_tail<NU, NU, NU>(sc, lane, kb ? N - kb_of(wb) * BLOCK : 0);
         return ka | kb << 1;
       } else {
-        mask_block(sc, w, second(follower));
-        return 3;
+        return mask_block(sc, w, second(follower));
       }
     };
     issue_tile(k_slot0, rk_at(w0), kp);
@@ -1142,7 +1152,7 @@ __device__ __forceinline__ void attn_tile(
     compute_scores<NU>(k_lds, qf, sc, fa);   // S(0)
     int keep = mask_step(sc, w0, o0, upper);
     Probs<NU> pr;
-    if (lead) softmax_phase<NU>(sc, ws, pr, scale_log2, nullptr);   // P(0)
+    if (lead) softmax_phase<NU, false>(sc, ws, pr, scale_log2, StepLoads{});   // P(0)
     __syncthreads();
     for (int j = 0; j < n; ++j) {
       // Word of step j+3 from the walk's LDS, read now and used at the end of
@@ -1154,27 +1164,28 @@ __device__ __forceinline__ void attn_tile(
       const StepLoads sl{
           (uint32_t)__builtin_amdgcn_readfirstlane(k_slot0 + (uint32_t)(j & 1) * TL::BYTES),
           (uint32_t)__builtin_amdgcn_readfirstlane(v_slot0 + (uint32_t)((j + 1) & 1) * TL::BYTES),
-          rk_at(w2), rv_at(w1), &kp, &vp};
+          rk_at(w2), rv_at(w1), kp, vp};
       const char* const kj1 = k_lds + ((j + 1) & 1) * TL::BYTES;   // K(j+1)
       const char* const vj = v_lds + (j & 1) * TL::BYTES;          // V(j)
-      // half-period 2j
+      // half-period 2j.  A leader whose query block does not keep the key block issues
+      // its loads up front (gemm_phase).
+      if (KG > 1 && SKIP && __builtin_amdgcn_readfirstlane(lead && !keep)) issue_step_loads(sl);
       if (lead) {
-        gemm_phase<NU, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep,
-                                   KG == 1 ? nullptr : &sl);
+        gemm_phase<NU, SKIP, (KG > 1)>(kj1, vj, qf, sc, pr, ws, fa, ones, keep, sl);
         keep = mask_step(sc, w1, o1, false);
       } else {
         if constexpr (KG == 1) issue_step_loads(sl);
-        softmax_phase<NU>(sc, ws, pr, scale_log2, KG == 1 ? nullptr : &sl);
+        softmax_phase<NU, (KG > 1)>(sc, ws, pr, scale_log2, sl);
       }
       __syncthreads();
       // half-period 2j+1
       if (lead) {
         if (j + 1 < n) {
           if constexpr (KG == 1) issue_step_loads(sl);
-          softmax_phase<NU>(sc, ws, pr, scale_log2, nullptr);
+          softmax_phase<NU, false>(sc, ws, pr, scale_log2, sl);
         }
       } else {
-        gemm_phase<NU, QUAD>(kj1, vj, qf, sc, pr, ws, fa, ones, keep, nullptr);
+        gemm_phase<NU, SKIP, false>(kj1, vj, qf, sc, pr, ws, fa, ones, keep, sl);
         keep = mask_step(sc, w1, o1, true);
       }
       wait_loads_and_sync();

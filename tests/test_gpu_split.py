@@ -232,23 +232,38 @@ def test_reference_is_raised_in_whole_tiles(form, block, v_exp):
     _check(out.float() * 2.0 ** -v_exp, ref, heads, N, block)
 
 
-def test_unkept_key_blocks_do_not_reach_a_query_block():
-    """Four 64-token query blocks share a tile; V of a key block that only the
-    first of them keeps may hold anything."""
-    H, N, block = 40, 64 * 29, 64
-    nb = N // block
-    q, k, v = make_qkv(H, N, seed=8)
-    v[:, 5 * block:6 * block] = float("nan")
-    keep = [[kb for kb in range(nb) if kb != 5 or qb % 4 == 0] for qb in range(nb)]
-    rp = torch.tensor([0] + np.cumsum([len(r) for r in keep]).tolist(), dtype=torch.int32)
-    ci = torch.tensor([kb for r in keep for kb in r], dtype=torch.int32)
-    m = L.csr_mask(rp.cuda(), ci.cuda(), N, block)
-    out = L.attention(q.cuda(), k.cuda(), v.cuda(), m)
+@pytest.mark.parametrize("form,block", [("block", 128), ("block", 64), ("exact", 128),
+                                        ("exact", 64)])
+@pytest.mark.parametrize("H,nb128", [(64, 8), (36, 14), (8, 17), (40, 15), (2, 8)])
+def test_unkept_key_blocks_do_not_reach_a_query_block(H, nb128, form, block):
+    """K and V of a key block may hold anything where a query block does not keep
+    it, in every kind of tile: whole ones (256 tiles), whole ones beside 64-row parts,
+    128-row parts, whole ones beside 128-row parts, 64-row parts.  Block form:
+    key block 5 is kept by the first of every four query blocks only; token-exact
+    form: frames of one block, of which frame 5 is attended by itself only."""
+    nb = nb128 * 128 // block
+    N = nb * block
+    _say(f"[split] unkept V {form} B={block} H={H} N={N}")
+    q, k, v = (x.cuda() for x in make_qkv(H, N, seed=8))
+    for x in (k, v):
+        x[:, 5 * block:6 * block] = float("nan")
+    if form == "block":
+        keep = [[kb for kb in range(nb) if kb != 5 or qb % 4 == 0] for qb in range(nb)]
+        rp = torch.tensor([0] + np.cumsum([len(r) for r in keep]).tolist(), dtype=torch.int32)
+        ci = torch.tensor([kb for r in keep for kb in r], dtype=torch.int32)
+        out = L.attention(q, k, v, L.csr_mask(rp.cuda(), ci.cuda(), N, block))
+        keeps = [qb % 4 == 0 for qb in range(nb)]
+    else:
+        csr = L.build_mask(nb, block, block, 0, L.Params(window=0, window_mode=L.WINDOW_BASIC,
+                                                         tper=4), exact=True)
+        csr.upload()
+        out = L.attention_exact(q, k, v, csr.exact_mask())
+        keeps = [qb == 5 for qb in range(nb)]
     torch.cuda.synchronize()
-    bad = torch.isnan(out.float()).any(-1).view(H, nb, block).any(-1).any(0).cpu().tolist()
-    # Whole tiles (all but the last head's, which may be split) keep them apart.
-    assert bad[0::4] == [True] * len(bad[0::4])
-    assert not any(bad[i] for i in range(nb) if i % 4 in (2, 3))
+    nan = torch.isnan(out.float()).view(H, nb, block * 128)
+    want = torch.tensor(keeps, device="cuda").expand(H, nb)
+    assert torch.equal(nan.all(-1), want)    # its own query blocks, in every head
+    assert torch.equal(nan.any(-1), want)    # and no other
 
 
 def test_counted_launches_in_graphs_and_streams():
