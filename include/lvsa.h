@@ -323,8 +323,10 @@ typedef struct lvsa_tensor {
  * its tile's query blocks in LDS).  Rows i >= N of `out` are never written;
  * a query block whose row is empty gets zeros, and key blocks that its row does
  * not hold never reach it, whatever their K and V hold.  out must not overlap q, k or
- * v.  The result is deterministic: for given heads, tokens and block, the keys
- * of a row are taken in a fixed order, whichever workgroup computes it.
+ * v.  The result is deterministic: for given heads, tokens, block and mask and
+ * a given number of compute units, the keys of a row are taken in a fixed order,
+ * whichever workgroup computes it.  Another number of heads (a shard of a layer)
+ * may split a row's keys into other partial sums: its last bits can differ.
  * Errors: EINVAL (nulls, shape mismatch), EUNSUPPORTED (head_dim, block,
  * alignment), ENOMEM (tile counters), EDEVICE (launch). */
 lvsa_status lvsa_attention(const lvsa_tensor* q, const lvsa_tensor* k,

@@ -273,6 +273,14 @@ __device__ __forceinline__ void wait_loads_and_sync() {
   __syncthreads();
 }
 
+// Time of a part of 256 / KG rows, in percent of a whole tile's (256 rows) of the same
+// walk (make_plan).
+constexpr int PART_TIME[] = {0, 100, 60, 0, 42};
+// What the parts of a tile take more in fixed times than the tile whole, in words of
+// its walk (64 keys): a whole tile's fixed time is that of 2.5 steps of 128 keys, a part's
+// 2.2 (64 rows) to 3.8 (128 rows), by the same measurements.
+constexpr int PARTS_FIXED = 12;
+
 // Scores of the wave's 32 query rows (two tiles of 16) against its keys, 16
 // keys per tile: lane l holds query rows l%16 of both tiles and keys
 // 16*kt + 4*(l/16) + r.
@@ -663,6 +671,14 @@ __device__ __forceinline__ void gemm_phase(const char* lds_k, const char* lds_v,
       }
 }
 
+// The thread's index, through an opaque move: what a tile derives from it is derived
+// again by the next one instead of being kept, and spilled, across the tile.
+__device__ __forceinline__ int fresh_tid() {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  return tid;
+}
+
 // LDS of the merged walk: the step words of the tile's pair of query blocks
 // (kept for the whole tile) and per-wave counts of the merge.  The merge's
 // inputs, the two CSR rows, are staged in the K/V tile buffers, which are
@@ -711,7 +727,7 @@ __device__ __forceinline__ int32_t merge_pair(WalkLds& L, uint32_t* stage,
                                               const uint32_t* __restrict__ rows,
                                               int32_t lo0, int32_t hi0, int32_t lo1,
                                               int32_t hi1, int32_t nb) {
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+  const int tid = fresh_tid(), lane = tid % 64, wave = tid / 64;
   constexpr int NWAVE = NT / 64;
   uint32_t* const sa = stage;              // row 0, largest key first
   uint32_t* const sb = stage + WALK_CAP;   // row 1
@@ -790,10 +806,13 @@ __device__ __forceinline__ int32_t merge_pair(WalkLds& L, uint32_t* stage,
 // the number of blocks above it in their union.  Words: kb in bits 0..27, bit
 // 28 + i set when row i keeps kb; entries outside [0, nb) are skipped, and at
 // most WALK_CAP entries of a row are read.  Returns the number of words (starts
-// and ends with a barrier).
+// and ends with a barrier); `apart`: the words that parts of PART query blocks
+// (1 or 2) would walk, all together.
+template <int PART>
 __device__ __forceinline__ int32_t merge_four(WalkLds& L, uint32_t* stage,
                                               const uint32_t* __restrict__ rows,
-                                              const int32_t (&rp)[5], int32_t nb) {
+                                              const int32_t (&rp)[5], int32_t nb,
+                                              int32_t& apart) {
   constexpr int WORDS = 256;                 // of 32 key blocks: WALK_CAP / 32, rounded up
   static_assert(WORDS * 32 >= WALK_CAP, "bitmap size");
   const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
@@ -813,26 +832,31 @@ __device__ __forceinline__ int32_t merge_four(WalkLds& L, uint32_t* stage,
   // Threads 0..255 hold the words last to first; blocks before a thread's
   // word in that order are the blocks above it.
   const int w = WORDS - 1 - tid;
-  int cnt = 0, incl = 0;
+  // Counts of both kinds in one scan: the union's in the low half (at most 8192),
+  // the parts' in the high half (at most 32768).
+  uint32_t cnt = 0, incl = 0;
   if (tid < WORDS) {
-    const uint32_t u = bm[w] | bm[WORDS + w] | bm[2 * WORDS + w] | bm[3 * WORDS + w];
+    const uint32_t r0 = bm[w], r1 = bm[WORDS + w], r2 = bm[2 * WORDS + w], r3 = bm[3 * WORDS + w];
+    const uint32_t u = r0 | r1 | r2 | r3;
     all[w] = u;
-    cnt = __popc(u);
+    const int ap = PART == 2 ? __popc(r0 | r1) + __popc(r2 | r3)
+                             : __popc(r0) + __popc(r1) + __popc(r2) + __popc(r3);
+    cnt = (uint32_t)__popc(u) | (uint32_t)ap << 16;
     incl = cnt;
     for (int off = 1; off < 64; off <<= 1) {
-      const int y = __shfl_up(incl, off);
+      const uint32_t y = __shfl_up(incl, off);
       if (lane >= off) incl += y;
     }
-    if (lane == 63) L.cnt[0][wave][0] = incl;
+    if (lane == 63) L.cnt[0][wave][0] = (int32_t)incl;
   }
   __syncthreads();
-  int words = 0;
+  uint32_t total = 0;
   for (int v = 0; v < WORDS / 64; ++v) {
-    const int c = L.cnt[0][v][0];
+    const uint32_t c = (uint32_t)L.cnt[0][v][0];
     if (v < wave) incl += c;
-    words += c;
+    total += c;
   }
-  if (tid < WORDS) above[w] = incl - cnt;
+  if (tid < WORDS) above[w] = (int32_t)((incl - cnt) & 0xFFFFu);
   __syncthreads();
   for (int kb = tid; kb < nb; kb += Tile::NT) {
     const uint32_t rest = all[kb / 32] >> (kb % 32);   // this block and those above it
@@ -843,7 +867,9 @@ __device__ __forceinline__ int32_t merge_four(WalkLds& L, uint32_t* stage,
     L.w[above[kb / 32] + __popc(rest >> 1)] = word;
   }
   __syncthreads();   // the words are written; the stage buffers are free again
-  return __builtin_amdgcn_readfirstlane(words);
+  total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
+  apart = (int32_t)(total >> 16);
+  return (int32_t)(total & 0xFFFFu);
 }
 
 // The step words of a tile that lies in one query block: its CSR row, largest
@@ -930,8 +956,15 @@ __device__ __forceinline__ void combine_groups(char* xch, WaveState& st, const f
 // One tile: rows row0 .. row0 + ROWS - 1 of head `head`, using the
 // workgroup's LDS stages `lds` (K slots 0-1, V slots 0-1).  The tile lies in
 // one query block or covers two or four whole ones.
-template <int BLOCK, int MODE, int KG>
-__device__ __forceinline__ void attn_tile(
+// Returns false, with nothing done, where parts of KGP key groups (KGP > KG) take
+// less time than the tile whole: a tile of four query blocks walks the union of their
+// rows, and where these have little in common the walks of the parts, each at its
+// share of a whole tile's time (PART_TIME), are the shorter ones.  Measured, 64-token
+// blocks, 12 heads of 32,768 tokens, 10% of the blocks kept: rows alike in pairs and
+// independent otherwise 0.75 ms against 0.98 with whole tiles only, all independent
+// 1.19 and 1.69 ms, rows alike in fours (whole tiles) 0.60 either way.
+template <int BLOCK, int MODE, int KG, int KGP>
+__device__ __forceinline__ bool attn_tile(
     char* lds, WalkLds& walk, int head, int row0, const __bf16* __restrict__ qg,
     const __bf16* __restrict__ kg_, const __bf16* __restrict__ vg, __bf16* __restrict__ og,
     int64_t q_sh, int64_t q_st, int64_t k_sh, int64_t k_st, int64_t v_sh, int64_t v_st,
@@ -955,7 +988,7 @@ __device__ __forceinline__ void attn_tile(
   constexpr uint32_t KB_MASK = EXACT ? 0xFFFFu : QUAD ? 0x0FFFFFFFu : 0x3FFFFFFFu;
   const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void*)lds;
 
-  const int tid = threadIdx.x;
+  const int tid = SPARSE ? fresh_tid() : (int)threadIdx.x;
   const int wave = tid / 64;
   const int lane = tid % 64;
   const int g16 = lane / 16;
@@ -1056,7 +1089,9 @@ __device__ __forceinline__ void attn_tile(
 #pragma unroll
         for (int i = 2; i < 5; ++i)
           rp[i] = __builtin_amdgcn_readfirstlane(row_ptr[min(qb0 + i, nb)]);
-        words = merge_four(walk, (uint32_t*)lds, rows, rp, nb);
+        int32_t apart = 0;
+        words = merge_four<4 / KGP>(walk, (uint32_t*)lds, rows, rp, nb, apart);
+        if (KGP > KG && 100 * (words - PARTS_FIXED) > PART_TIME[KGP] * apart) return false;
       } else if constexpr (PAIR) {
         const int32_t r2 =
             qb0 + 1 < nb ? __builtin_amdgcn_readfirstlane(row_ptr[qb0 + 2]) : r1;
@@ -1220,6 +1255,7 @@ __device__ __forceinline__ void attn_tile(
       }
     }
   }
+  return true;
 }
 
 // First item and item count of XCD x's share of `total` items: contiguous
@@ -1284,12 +1320,22 @@ struct KArgs {
   float scale_log2;
 };
 
-template <int BLOCK, int MODE, int KG>
-__device__ __forceinline__ void attn_tile_args(char* lds, WalkLds& walk, int head, int row0,
+template <int BLOCK, int MODE, int KG, int KGP>
+__device__ __forceinline__ bool attn_tile_args(char* lds, WalkLds& walk, int head, int row0,
                                                const KArgs& a) {
-  attn_tile<BLOCK, MODE, KG>(lds, walk, head, row0, a.q, a.k, a.v, a.o, a.q_sh, a.q_st, a.k_sh,
-                             a.k_st, a.v_sh, a.v_st, a.o_sh, a.o_st, a.N, a.nb, a.row_ptr,
-                             a.rows, a.P, a.scale_log2);
+  return attn_tile<BLOCK, MODE, KG, KGP>(lds, walk, head, row0, a.q, a.k, a.v, a.o, a.q_sh,
+                                         a.q_st, a.k_sh, a.k_st, a.v_sh, a.v_st, a.o_sh, a.o_st,
+                                         a.N, a.nb, a.row_ptr, a.rows, a.P, a.scale_log2);
+}
+
+// The kernel's arguments (its first), read through an offset that the compiler
+// cannot see to be zero: every tile loads them afresh (scalar loads), so they are
+// not live across tiles.
+__device__ __forceinline__ const KArgs* fresh_args() {
+  int zero = 0;
+  asm volatile("" : "+v"(zero));
+  zero = __builtin_amdgcn_readfirstlane(zero);
+  return (const KArgs*)((const char*)__builtin_amdgcn_kernarg_segment_ptr() + zero);
 }
 
 // Persistent workgroups, at most one per CU, take items until all are done
@@ -1304,6 +1350,8 @@ __global__ __launch_bounds__(Tile::NT) void attn_fwd_kernel(const KArgs args) {
   __shared__ WalkLds walk;
   __shared__ int next_item;
   constexpr int PARTS = KGS / KGW;
+  // attn_tile may refuse whole tiles of four query blocks.
+  constexpr bool REFUSES = MODE == ATTN_BLOCK && Split<KGW>::ROWS == 4 * BLOCK && PARTS > 1;
   // Workgroups are dispatched round-robin over the 8 XCDs.
   const int xcd = blockIdx.x % 8;
   for (;;) {
@@ -1319,29 +1367,46 @@ __global__ __launch_bounds__(Tile::NT) void attn_fwd_kernel(const KArgs args) {
       item = __builtin_amdgcn_readfirstlane(
           share_item(xcd, (int)(blockIdx.x / 8), args.whole, args.split));
     }
-    // The arguments are the first kernel argument; an offset the compiler
-    // cannot see to be zero makes every tile load them afresh (scalar
-    // loads), so they are not live across tiles.
-    int zero = 0;
-    asm volatile("" : "+v"(zero));
-    zero = __builtin_amdgcn_readfirstlane(zero);
-    const KArgs* ap = (const KArgs*)((const char*)__builtin_amdgcn_kernarg_segment_ptr() + zero);
     // Tiles of a head go last to first: rows that attend every key block (text
     // tokens, placed after the video tokens) are the longest tiles, and taking
     // them first keeps them out of the grid's tail (each row's key blocks are
     // then walked in descending order, which keeps neighbouring workgroups'
     // shared blocks in L2).
-    if (item < ap->whole) {
-      const int p = ap->per_head - 1 - item % ap->per_head;
-      attn_tile_args<BLOCK, MODE, KGW>(lds, walk, item / ap->per_head,
-                                       p * Split<KGW>::ROWS, *ap);
-    } else if constexpr (PARTS > 1) {
-      const int u = item - ap->whole;
-      const int tile = ap->whole + u / PARTS;
-      const int p = ap->per_head - 1 - tile % ap->per_head;
-      const int row0 = p * Split<KGW>::ROWS + (PARTS - 1 - u % PARTS) * Split<KGS>::ROWS;
-      if (row0 < ap->N)
-        attn_tile_args<BLOCK, MODE, KGS>(lds, walk, tile / ap->per_head, row0, *ap);
+    if constexpr (REFUSES) {
+      // First and last part to work: one part, all parts of a whole tile that was
+      // refused (last to first), or none.
+      const KArgs* ap = fresh_args();
+      int i = -1, last = 0;
+      if (item >= ap->whole) {
+        i = last = PARTS - 1 - (item - ap->whole) % PARTS;
+      } else {
+        const int p = ap->per_head - 1 - item % ap->per_head;
+        if (!attn_tile_args<BLOCK, MODE, KGW, KGS>(lds, walk, item / ap->per_head,
+                                                   p * Split<KGW>::ROWS, *ap))
+          i = PARTS - 1;
+      }
+      for (; i >= last; --i) {
+        const KArgs* ap = fresh_args();
+        const int tile = item < ap->whole ? item : ap->whole + (item - ap->whole) / PARTS;
+        const int p = ap->per_head - 1 - tile % ap->per_head;
+        const int row0 = p * Split<KGW>::ROWS + i * Split<KGS>::ROWS;
+        if (row0 < ap->N)
+          attn_tile_args<BLOCK, MODE, KGS, KGS>(lds, walk, tile / ap->per_head, row0, *ap);
+      }
+    } else {
+      const KArgs* ap = fresh_args();
+      if (item < ap->whole) {
+        const int p = ap->per_head - 1 - item % ap->per_head;
+        attn_tile_args<BLOCK, MODE, KGW, KGW>(lds, walk, item / ap->per_head,
+                                              p * Split<KGW>::ROWS, *ap);
+      } else if constexpr (PARTS > 1) {
+        const int u = item - ap->whole;
+        const int tile = ap->whole + u / PARTS;
+        const int p = ap->per_head - 1 - tile % ap->per_head;
+        const int row0 = p * Split<KGW>::ROWS + (PARTS - 1 - u % PARTS) * Split<KGS>::ROWS;
+        if (row0 < ap->N)
+          attn_tile_args<BLOCK, MODE, KGS, KGS>(lds, walk, tile / ap->per_head, row0, *ap);
+      }
     }
     if (!args.counters) break;
   }

@@ -89,6 +89,41 @@ def test_random_csr_by_plan(H, N, block):
         assert bool((out[:, qb * block:(qb + 1) * block] == 0).all())
 
 
+@pytest.mark.parametrize("H,N", [(16, 4089), (21, 3200), (22, 3999)])
+def test_four_blocks_with_little_in_common(H, N):
+    """64-token blocks: whole tiles whose four rows are alike, alike in pairs, or
+    disjoint, some empty, side by side; those with little in common are worked in
+    parts.  256 whole tiles (no counters), whole tiles beside 64-row parts, and
+    beside 128-row parts."""
+    _say(f"[split] rows with little in common H={H} N={N}")
+    block = 64
+    q, k, v = make_qkv(H, N, seed=N)
+    nb = -(-N // block)
+    rng = np.random.default_rng(N)
+    rows = []
+    for qb in range(nb):
+        i, kind = qb % 4, qb // 4 % 4
+        if i == 0:
+            base = rng.permutation(nb)
+        cols = {0: base[: nb // 2], 1: base[i // 2::2], 2: base[i::4],
+                3: base[i::2] if i < 3 else []}[kind]
+        rows.append(sorted(int(x) for x in cols))
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    ci = np.asarray([x for r in rows for x in r], dtype=np.int32)
+    m = L.csr_mask(torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), N, block)
+    out = torch.full((H, N, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    L.attention(q.cuda(), k.cuda(), v.cuda(), m, out=out)
+    torch.cuda.synchronize()
+    heads = sorted({0, H // 2, H - 1})
+    qs, ks, vs = (x[heads].float().numpy() for x in (q, k, v))
+    full = [qb for qb in range(nb) if rows[qb]]
+    ref = OA.block_sparse_attention(qs, ks, vs, rp.tolist(), ci.tolist(), block, q_blocks=full)
+    _check(out, ref, heads, N, block)
+    for qb in set(range(nb)) - set(full):
+        assert bool((out[:, qb * block:(qb + 1) * block] == 0).all())
+    assert bool(torch.isfinite(out.float()).all())
+
+
 @pytest.mark.parametrize("block", [128, 64])
 @pytest.mark.parametrize("tiles", [2, 84])
 @pytest.mark.parametrize("steps", [1, 2, 3, 4, 5])
@@ -234,7 +269,7 @@ def test_reference_is_raised_in_whole_tiles(form, block, v_exp):
 
 @pytest.mark.parametrize("form,block", [("block", 128), ("block", 64), ("exact", 128),
                                         ("exact", 64)])
-@pytest.mark.parametrize("H,nb128", [(64, 8), (36, 14), (8, 17), (40, 15), (2, 8)])
+@pytest.mark.parametrize("H,nb128", [(64, 8), (40, 15), (8, 17), (44, 16), (2, 8)])
 def test_unkept_key_blocks_do_not_reach_a_query_block(H, nb128, form, block):
     """K and V of a key block may hold anything where a query block does not keep
     it, in every kind of tile: whole ones (256 tiles), whole ones beside 64-row parts,

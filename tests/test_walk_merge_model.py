@@ -1,6 +1,9 @@
-"""CPU model of the position rule by which the attention kernel merges the two
-CSR rows of a pair of query blocks into one walk (host logic; the kernel itself
-is checked on the GPU by test_gpu_attention.py's caller-CSR tests).
+"""CPU models of the position rules by which the attention kernel merges the
+CSR rows of two or four query blocks into one walk (host logic; the kernel itself
+is checked on the GPU by the caller-CSR tests of test_gpu_attention.py and
+test_gpu_split.py).
+
+Two rows (merge_pair):
 
 The kernel stages both rows largest key first and places every entry of the
 union at: its index in its own row, plus the entries of the other row with a
@@ -134,3 +137,76 @@ def test_out_of_range_keys_give_words_that_mask_everything():
     assert got == union_words(r0, r1, nb, False)
     assert got[:2] == [0x3FFFFFFF, 0x3FFFFFFF]
     assert got[2:] == [9 | 1 << 31, 4 | 3 << 30, 1 | 1 << 30]
+
+
+# Four rows (merge_four): a bitmap of 32-block words per row; a block's place is the
+# number of union blocks above it: those in the words after its own (a scan from
+# the last word on), then those above it in its word.  The same scan, in the high
+# half of its counts, gives the words that the tile's parts would walk.
+WORDS = 256
+PART_TIME = {2: 60, 1: 42}      # by query blocks per part, percent of a whole tile's time
+PARTS_FIXED = 12
+
+
+def merge_four_model(rows, nb, part):
+    bm = [[0] * WORDS for _ in range(4)]
+    for i, row in enumerate(rows):
+        for kb in row[-WALK_CAP:]:
+            if 0 <= kb < nb:
+                bm[i][kb // 32] |= 1 << (kb % 32)
+    every = [a | b | c | d for a, b, c, d in zip(*bm)]
+    above, incl = [0] * WORDS, 0
+    for w in reversed(range(WORDS)):
+        a, b, c, d = (bm[i][w] for i in range(4))
+        apart = (bin(a | b).count("1") + bin(c | d).count("1") if part == 2
+                 else sum(bin(x).count("1") for x in (a, b, c, d)))
+        above[w] = incl & 0xFFFF
+        incl += bin(every[w]).count("1") | apart << 16
+        assert incl < 1 << 32
+    out = [None] * (incl & 0xFFFF)
+    for kb in range(nb):
+        rest = every[kb // 32] >> (kb % 32)
+        if rest & 1:
+            word = kb
+            for i in range(4):
+                word |= ((bm[i][kb // 32] >> (kb % 32)) & 1) << (28 + i)
+            out[above[kb // 32] + bin(rest >> 1).count("1")] = word
+    return out, incl >> 16
+
+
+def _refused(words, apart, part):
+    return 100 * (words - PARTS_FIXED) > PART_TIME[part] * apart
+
+
+def test_four_row_merge_gives_the_union_and_the_parts_words():
+    rng = random.Random(12)
+    cases = []
+    for _ in range(60):
+        nb = rng.choice([1, 2, 5, 31, 32, 33, 300, 1475, 3000])
+        cases.append((nb, [_row(rng, nb, rng.choice([0, 1, nb, rng.randint(0, nb)]), False)
+                           for _ in range(4)]))
+    nb = WALK_CAP
+    full = list(range(nb))
+    cases += [(nb, [full] * 4), (nb, [full[i::4] for i in range(4)]), (nb, [[], full, [], []]),
+              (nb, [[]] * 4), (10, [[1, 4, 12], [9, 30], [], [4]])]    # keys past nb: skipped
+    for nb, rows in cases:
+        kept = [{kb for kb in r if kb < nb} for r in rows]
+        want = [kb | sum(1 << (28 + i) for i in range(4) if kb in kept[i])
+                for kb in sorted(set().union(*kept), reverse=True)]
+        pairs = len(kept[0] | kept[1]) + len(kept[2] | kept[3])
+        for part, apart in ((2, pairs), (1, sum(map(len, kept)))):
+            assert merge_four_model(rows, nb, part) == (want, apart)
+
+
+def test_tiles_of_rows_with_little_in_common_are_refused():
+    """The rows of an LVSA mask stay in one tile, disjoint rows do not, and walks too
+    short to pay for the parts' fixed times stay whole."""
+    n = 200
+    a, b, c, d = ([*range(i, 4 * n, 4)] for i in range(4))
+    for part in (1, 2):
+        for rows, want in [([a] * 4, False), ([a, b, c, d], True), ([a[:1], b[:1], c[:1], d[:1]],
+                                                                    False),
+                           ([a, a, b, b], True), ([a, a[:-4], a[4:], a], False),
+                           ([[]] * 4, False)]:
+            words, apart = merge_four_model(rows, 4 * n, part)
+            assert _refused(len(words), apart, part) == want, (part, want)
