@@ -211,9 +211,10 @@ def test_edge_shapes(T, P, B, H, W, tper):
 
 @pytest.mark.parametrize("scale", [8.0, 30.0])
 def test_large_logits_exercise_the_rescale(scale):
-    """Q and K scaled up so logits span hundreds of log2 units: the running
-    max is raised on most key blocks (the rescale of O and l runs often) and
-    the result still matches the fp32 oracle."""
+    """Q and K scaled up so logits span hundreds of log2 units: the rows'
+    references are raised again and again (with O and l rescaled and the step's
+    probabilities done again) and the result still matches the fp32 oracle.
+    These launches run as parts of tiles; whole tiles are in test_gpu_split.py."""
     T, P, B, H = 6, 200, 128, 2
     N = T * P
     _say(f"[large-logits] scale {scale}")
@@ -237,15 +238,19 @@ def test_large_logits_exercise_the_rescale(scale):
     assert_close(float(err.max()), float(err.mean()))
 
 
+@pytest.mark.parametrize("H", [2, 26])
 @pytest.mark.parametrize("T,P,B,exact", [(9, 150, 64, False), (9, 150, 64, True),
                                          (12, 200, 128, False), (12, 200, 128, True)])
-def test_pairs_whose_rows_differ(T, P, B, exact):
-    """The kernel walks query blocks in pairs over the union of their key
-    lists; where a frame edge falls between the two blocks their rows differ
-    and each block's waves must drop the other's extra key blocks.  Shapes
-    where that happens in most pairs (narrow windows, P not a multiple of B),
-    both forms, against the oracle over every row."""
-    H, W, tper = 2, 0, 5
+def test_pairs_whose_rows_differ(T, P, B, exact, H):
+    """A whole tile walks its query blocks (two, or four of 64 tokens in the block
+    form) over the union of their key lists; where a frame edge falls between
+    two blocks their rows differ and each block's waves must drop the other's
+    extra key blocks.  Shapes where that happens in most pairs (narrow windows,
+    P not a multiple of B), both forms, against the oracle over every row of the
+    first and last heads.  26 heads are planned as 256 whole tiles and parts of the
+    rest (156 whole tiles for 64-token blocks in the block form); 2 heads as parts
+    of one query block or one pair."""
+    W, tper = 0, 5
     N = T * P
     p = L.Params(window=W, tper=tper)
     _say(f"[pairs] T={T} P={P} B={B} exact={exact}")
@@ -259,7 +264,8 @@ def test_pairs_whose_rows_differ(T, P, B, exact):
     q, k, v = make_qkv(H, N, seed=T * 10 + B)
     qd, kd, vd = (x.cuda() for x in (q, k, v))
     csr.upload()
-    qf, kf, vf = (x.float().numpy() for x in (q, k, v))
+    heads = [0, H - 1]
+    qf, kf, vf = (x[heads].float().numpy() for x in (q, k, v))
     if exact:
         out = L.attention_exact(qd, kd, vd, csr.exact_mask())
         _, _, A = M.attended_frames(T, 2, W=W, tper=tper)
@@ -267,9 +273,9 @@ def test_pairs_whose_rows_differ(T, P, B, exact):
     else:
         out = L.attention(qd, kd, vd, csr.device_mask())
         ref = OA.assemble(OA.block_sparse_attention(qf, kf, vf, rp.tolist(), ci.tolist(), B),
-                          H, N, 128, B)
+                          2, N, 128, B)
     torch.cuda.synchronize()
-    err = np.abs(out.float().cpu().numpy() - ref)
+    err = np.abs(out[heads].float().cpu().numpy() - ref)
     assert_close(float(err.max()), float(err.mean()))
 
 
@@ -287,11 +293,13 @@ def _random_csr(nb, rng, min_len=1, max_len=None):
 
 
 @pytest.mark.parametrize("T,P,B,H,seed", [(6, 200, 128, 2, 1), (9, 150, 64, 2, 2),
-                                          (20, 512, 128, 3, 3), (7, 190, 128, 1, 4)])
+                                          (20, 512, 128, 3, 3), (7, 190, 128, 1, 4),
+                                          (20, 512, 128, 7, 5)])
 def test_random_csr_matches_oracle(T, P, B, H, seed):
     """Attention over a caller-built CSR (lvsa_attention reads any block CSR):
-    rows of 1 to nb blocks, the two rows of a pair different, a ragged last
-    block; every row against the oracle."""
+    rows of 1 to nb blocks, neighbouring rows different, a ragged last block;
+    every row against the oracle.  The last shape is planned as 256 whole tiles
+    (pairs of rows, merged) and parts of one row; the others as parts."""
     N = T * P
     nb = -(-N // B)
     rng = np.random.default_rng(seed)
@@ -310,10 +318,13 @@ def test_random_csr_matches_oracle(T, P, B, H, seed):
     assert_close(float(err.max()), float(err.mean()))
 
 
-def test_random_csr_one_block_rows_and_full_rows():
+@pytest.mark.parametrize("H", [2, 33])
+def test_random_csr_one_block_rows_and_full_rows(H):
     """Extremes of a caller CSR: every even row keeps one block, every odd row
-    keeps all nb, so each pair walks nb blocks of which one is shared."""
-    T, P, B, H = 8, 256, 128, 2
+    keeps all nb, so a merged pair walks nb blocks of which one is shared.  33
+    heads are planned as whole tiles (pairs) and parts, 2 heads as parts of one
+    row."""
+    T, P, B = 8, 256, 128
     N = T * P
     nb = N // B
     rng = np.random.default_rng(7)
@@ -336,10 +347,10 @@ def test_random_csr_one_block_rows_and_full_rows():
 
 def test_csr_at_the_block_limit():
     """nb = 8000 key blocks (B = 64), the most the sparse kernels take: rows 0
-    and 1 keep every block (their merged walk fills the 8000-word LDS array
-    over 16 merge passes), the last pair keeps different blocks in each row,
-    the others keep the diagonal and two random blocks; sampled query blocks
-    against the oracle."""
+    and 1 keep every block (the merged walk of the first four rows fills the
+    8000-word LDS array), the last pair keeps different blocks in each row, the
+    others keep the diagonal and two random blocks; sampled query blocks against
+    the oracle."""
     B, H, nb = 64, 1, 8000
     N = nb * B - 19                     # ragged last block
     rng = np.random.default_rng(8000)
@@ -364,10 +375,75 @@ def test_csr_at_the_block_limit():
     assert_close(*compare_rows(out, q, k, v, rp, ci, B, [0], [0, 1, 2, 4001, nb - 2, nb - 1]))
 
 
-def test_empty_rows_give_zeros():
-    """A query block whose CSR row is empty gets zeros; its pair partner is
-    unaffected."""
-    T, P, B, H = 4, 256, 128, 1
+@pytest.mark.parametrize("form,block,nb", [("block", 128, 8000), ("block", 64, 8000),
+                                           ("exact", 64, 8000), ("exact", 128, 3000)])
+def test_merges_of_long_rows_that_differ(form, block, nb):
+    """Rows of thousands of entries that differ, in whole tiles (the launches have
+    thousands of tiles, these rows lie in the middle): two rows are merged over up
+    to 16 passes whose counts carry from one to the next, four through bitmaps of
+    up to 8000 key blocks.  Groups of four query blocks whose rows are disjoint and
+    interleaved, random and overlapping, or empty beside full; token-exact entry
+    words with every pattern.  All other rows keep their diagonal block."""
+    H, P = 1, 300
+    N = nb * block - 21
+    rng = np.random.default_rng(nb + block)
+    rows = [[r] for r in range(nb)]
+    groups = [nb // 4 // 4 * 4, nb // 2 // 4 * 4, nb // 4 * 3 // 4 * 4]
+    step = 2 if form == "exact" or block == 128 else 4
+    for i in range(4):
+        rows[groups[0] + i] = list(range(i % step, nb, step))
+        rows[groups[1] + i] = np.flatnonzero(rng.random(nb) < (0.7, 0.4, 0.9, 0.1)[i]).tolist()
+        rows[groups[2] + i] = [] if i % 2 else list(range(nb))
+    picks = [g + i for g in groups for i in range(4) if rows[g + i]] + [0, nb - 1]
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    ci = np.asarray([kb for r in rows for kb in r], dtype=np.int64)
+    _say(f"[long-merge] {form} N={N} B={block} nb={nb} nnz={len(ci)}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(81)
+    q, k, v = (torch.randn((H, N, 128), generator=g, device="cuda").to(torch.bfloat16)
+               for _ in range(3))
+    rpd = torch.from_numpy(rp).cuda()
+    # Key block kb's first `first[kb]` tokens lie in its first frame (all of them
+    # where it touches one frame only).
+    start = np.arange(nb) * block
+    first = np.minimum(P - start % P, block)
+    if form == "block":
+        pat = np.full(len(ci), 15)
+        out = L.attention(q, k, v, L.csr_mask(rpd, torch.from_numpy(ci.astype(np.int32)).cuda(), N,
+                                              block))
+    else:
+        pat = rng.integers(1, 16, size=len(ci))
+        entry = torch.from_numpy((ci | first[ci] << 16 | pat << 24).astype(np.int32)).cuda()
+        out = L.attention_exact(q, k, v, L.exact_csr_mask(rpd, entry, N, block, P))
+    torch.cuda.synchronize()
+    worst, total, count = 0.0, 0.0, 0
+    kf, vf = (x[0].float() for x in (k, v))
+    for qb in picks:
+        lo, hi = rp[qb], rp[qb + 1]
+        keys = torch.from_numpy((ci[lo:hi, None] * block + np.arange(block)).ravel()).cuda()
+        part = torch.from_numpy((np.arange(block) >= first[ci[lo:hi], None]).ravel()).cuda()
+        bits = torch.from_numpy(np.repeat(pat[lo:hi], block)).cuda()
+        ok = keys < N
+        keys, part, bits = keys[ok], part[ok].long(), bits[ok]
+        i = torch.arange(qb * block, min((qb + 1) * block, N), device="cuda")
+        second = (i - qb * block >= first[qb]).long()
+        keep = (bits[None] >> (2 * second[:, None] + part[None])) & 1
+        s = q[0, i].float() @ kf[keys].t() / 128 ** 0.5
+        s = s.masked_fill(keep == 0, float("-inf"))
+        ref = torch.softmax(s, -1).nan_to_num(0.0) @ vf[keys]
+        err = (out[0, i].float() - ref).abs()
+        worst, total, count = max(worst, err.max().item()), total + err.sum().item(), count + err.numel()
+    assert_close(worst, total / count)
+    for i in (1, 3):
+        r = groups[2] + i
+        assert bool((out[0, r * block:(r + 1) * block] == 0).all())
+
+
+@pytest.mark.parametrize("H", [1, 66])
+def test_empty_rows_give_zeros(H):
+    """A query block whose CSR row is empty gets zeros; its neighbours are
+    unaffected (66 heads: whole tiles of two query blocks, and parts)."""
+    T, P, B = 4, 256, 128
     N = T * P
     nb = N // B
     rp, ci = [0], []
@@ -385,8 +461,8 @@ def test_empty_rows_give_zeros():
     keep = [r for r in range(nb) if r not in (2, 5, 6)]
     ref = OA.block_sparse_attention(q.float().numpy(), k.float().numpy(), v.float().numpy(),
                                     rp, ci, B, q_blocks=keep)
-    worst = max(float(np.abs(out[0, qb * B:(qb + 1) * B] - r).max())
-                for (_, qb), r in ref.items())
+    worst = max(float(np.abs(out[h, qb * B:(qb + 1) * B] - r).max())
+                for (h, qb), r in ref.items())
     assert worst <= 2e-2
 
 

@@ -63,9 +63,8 @@ def test_exact_full_output_matches_eq2(T, P, B, H, W, tper):
 
 def test_exact_equals_block_mode_when_block_divides_frame():
     """P mod B = 0: every kept block is whole, so the two forms attend the
-    same keys with the same scores and probabilities.  They keep the row sums
-    differently (fp32 adds of the probabilities in the block form, matrix-core
-    sums of their bf16 values in the token-exact form), which moves the
+    same keys with the same scores, probabilities and row sums.  The launch plan
+    may split a row's keys differently in the two forms, which moves the
     normalised output by far less than half a bf16 unit: the two agree to one
     unit in the last place of bf16."""
     w = WORKLOADS["tiny"]
