@@ -327,6 +327,8 @@ typedef struct lvsa_tensor {
  * a given number of compute units, the keys of a row are taken in a fixed order,
  * whichever workgroup computes it.  Another number of heads (a shard of a layer)
  * may split a row's keys into other partial sums: its last bits can differ.
+ * V of magnitudes below 2^-100 loses precision where a row's scores (natural
+ * logarithm) exceed those of the keys taken first by more than 5.
  * Errors: EINVAL (nulls, shape mismatch), EUNSUPPORTED (head_dim, block,
  * alignment), ENOMEM (tile counters), EDEVICE (launch). */
 lvsa_status lvsa_attention(const lvsa_tensor* q, const lvsa_tensor* k,

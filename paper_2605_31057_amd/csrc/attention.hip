@@ -20,7 +20,8 @@
 //   host plans which tiles run how (make_plan).
 //   One persistent workgroup per compute unit takes items through atomic
 //   counters (fetch_item); a launch with a workgroup for every item has no
-//   counters.
+//   counters.  A whole tile of four query blocks whose rows have little in common
+//   is worked in its parts by the workgroup that took it (attn_tile).
 //
 // The merged walk
 //   A tile's key blocks are the union of its query blocks' CSR rows, walked in
@@ -80,9 +81,9 @@
 //   the softmax phase (112 VALU instructions and 64 exponentials a step beside
 //   136 MFMAs, and 8 tile loads of about 67 cycles) takes 2,700 cycles, and the
 //   GEMM phase (136 MFMAs of 16 cycles, 96 LDS reads of about 2.3) 2,600.
-//   Wan-1.3B 6x, 12 heads, step 10: 30.7 ms with 32x32x16 MFMAs and a row
-//   maximum per step, 27.6 ms now (1.45 PFLOP/s; a large bf16 matrix product
-//   reaches 1.62 on this card), interleaved on one board.
+//   Wan-1.3B 6x, 12 heads, step 10: 31.9 ms with 32x32x16 MFMAs and a row
+//   maximum per step, 28.9 ms now (1.38 PFLOP/s; a large bf16 matrix product
+//   reaches 1.54), all on one board, one of the slower ones.
 //
 // Online softmax (fp32, base 2): p = exp2(s*log2(e)/sqrt(d) - m), l = sum p,
 // with a reference m per row that is raised, and O and l rescaled, only when
@@ -527,10 +528,13 @@ __device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU
 // lanes.  The result is exact either way because O and l always use the same
 // m.  Until every row has an m (READY), m is raised first.
 //
-// The headroom is 7 at first: products p v then keep their bits for v down to
-// 2^-130.  Logits so wide that a step is redone would cross it again and again
+// The headroom is 7 at first: the result is then as precise as against the running
+// maximum for V of any scale (measured down to 2^-120, where bf16 itself runs out).
+// Logits so wide that a step is redone would cross it again and again
 // (one redoing wave holds up the other seven at the half step's barrier), so the
-// wave's first redo takes 39 from then on, for v down to 2^-100.  Wan-1.3B 6x
+// wave's first redo takes 39 from then on; products p v then lose bits for v below
+// 2^-100 (measured, Q and K times 8: error 0.94e-3 down to 2^-95, 0.95e-3 at 2^-100,
+// 7.8e-3 at 2^-105).  Wan-1.3B 6x
 // step with Q and K times 1, 2, 4, 8, ms, interleaved on one board: 27.8, 29.9, 31.0
 // and 30.0 with 7 throughout, 27.7, 28.5, 28.6 and 28.5 so (with a row maximum every
 // step and 32x32x16 MFMAs 30.4, 31.8, 32.0 and 28.9).  Times 16 and more, where one
@@ -679,11 +683,11 @@ __device__ __forceinline__ int fresh_tid() {
   return tid;
 }
 
-// LDS of the merged walk: the step words of the tile's pair of query blocks
-// (kept for the whole tile) and per-wave counts of the merge.  The merge's
-// inputs, the two CSR rows, are staged in the K/V tile buffers, which are
-// idle at the start of a tile.  A pair's union has at most nb words, so
-// nb <= WALK_CAP (checked before launch) lets one merge cover the tile.
+// LDS of the merged walk: the step words of the tile's query blocks (kept for
+// the whole tile) and per-wave counts of the merge.  The merge's inputs, two CSR
+// rows or the bitmaps of four, are staged in the K/V tile buffers, which are idle
+// at the start of a tile.  The union of the rows has at most nb words, so nb <=
+// WALK_CAP (checked before launch) lets one merge cover the tile.
 constexpr int WALK_CAP = 8000;
 struct WalkLds {
   uint32_t w[WALK_CAP];       // step words, in walk order
@@ -691,8 +695,8 @@ struct WalkLds {
 };
 static_assert(2 * WALK_CAP * 4 <= 4 * Tile::BYTES, "rows staged in the tile buffers");
 
-// Step words.  Block form (row entries are key blocks): kb in bits 0..29,
-// bit 30 / 31 set when row 0 / row 1 keeps kb.  Token-exact form (row
+// Step words of one or two rows (of four: merge_four).  Block form (row entries are
+// key blocks): kb in bits 0..29, bit 30 / 31 set when row 0 / row 1 keeps kb.  Token-exact form (row
 // entries are entry words): bits 0..23 kb and kfirst, bits 24..27 / 28..31
 // the patterns of row 0 / row 1, 0 where that row does not keep kb.  A key
 // block outside [0, nb) gives a word that masks every key (and whose loads
@@ -1045,7 +1049,7 @@ __device__ __forceinline__ bool attn_tile(
   // Masks the scores of the key block of step word w for this wave's query
   // block: a key block that block does not keep has no valid keys.
   // `second`: the wave holds rows of query block 2p + 1.
-  // Returns whether the query block keeps it.
+  // Returns whether the wave's query block keeps it.
   auto mask_block = [&](Scores<NU>& sc, uint32_t w, bool second) -> int {
     const int kb = kb_of(w);
     const uint32_t kept_bit = second ? 31u : 30u;      // block form
@@ -1446,8 +1450,8 @@ int tiles_of(const AttnArgs& a, int kg) {
 // tile at a time, so a last round that is nearly empty costs as much as a full
 // one, and a launch of fewer tiles than CUs leaves CUs idle.  Splitting tiles
 // over the key groups of a workgroup (Split) gives more, shorter items: a
-// 128-row item takes 0.60 of a 256-row tile's time and a 64-row one 0.42 (not
-// 0.5 and 0.25: each K/V tile brought into LDS serves fewer rows; measured with
+// 128-row item takes 0.60 of a 256-row tile's time and a 64-row one 0.42
+// (PART_TIME; not 0.5 and 0.25: each K/V tile brought into LDS serves fewer rows; measured with
 // every CU busy, Wan-1.3B 1x and 6x: 4.48 and 28.7 ms whole, 5.28 and 33.3 ms in
 // 128-row items, 7.69 and 43.1 ms in 64-row items; with 64-token blocks at 2x 9.34,
 // 10.6 and 13.7 ms; walks of 16 steps 0.72 and 0.48, of 4 steps 0.94 and 0.61,

@@ -33,9 +33,9 @@ void build_csr_host(const FrameCfg& c, int32_t P, int32_t B,
                     std::vector<uint32_t>* entry);
 
 // Device mask construction (mask_device.hip).  Writes row_ptr and, where the
-// pointer is non-null, col_idx and/or the token-exact entry words.  A row's
-// frames are gone through one by one, so a query-block pair may touch 1024 of
-// them at most (device_mask_supported).
+// pointer is non-null, col_idx and/or the token-exact entry words.  Shapes in which
+// two adjacent query blocks may touch more than 1024 frames are refused, as
+// lvsa.h states (device_mask_supported).
 bool device_mask_supported(const FrameCfg& c, int32_t P, int32_t B);
 hipError_t launch_build_mask_device(const FrameCfg& c, int32_t P, int32_t B,
                                     int32_t* d_row_ptr, int32_t* d_col_idx,

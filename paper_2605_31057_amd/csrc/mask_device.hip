@@ -31,7 +31,9 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 
-// Frames that a query-block pair may touch (checked before launch).
+// Frames that two adjacent query blocks may touch (checked before launch): the
+// interface's limit.  Nothing here is sized by it; one thread goes through a row's
+// frames one by one (make_row), which is what such rows would cost.
 constexpr int kMaxRowFrames = 1024;
 
 // Key blocks: nb * nb fits in int32.
