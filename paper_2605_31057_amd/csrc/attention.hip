@@ -359,14 +359,13 @@ __device__ __forceinline__ void compute_scores(const char* lds_k, const bf16x8 (
 // and P's rounding largely cancels: with d_i the relative rounding of p_i the
 // result is off by sum d_i p_i (v_i - o) / l instead of sum d_i p_i v_i / l.
 // Measured, 2-norm of the error against float64 relative to the result, fp32 sums
-// (against the running maximum) and these: 22 shapes of N(0, 1) inputs in all
-// forms 2.29e-3 to 2.36e-3 and 2.25e-3 to 2.36e-3, not larger in any but one (an
-// exact one of 4 heads by 0.1%, in split tiles while those summed on the VALU);
-// one head of 4,680 tokens, split, with
-// Q and K times 1, 2, 4, 8, 16 2.36e-3, 2.07e-3, 1.77e-3, 1.07e-3, 0.56e-3 and
-// 2.36e-3, 1.82e-3, 1.51e-3, 0.93e-3, 0.49e-3, and 12 heads of 5,460, whole,
-// 2.33e-3, 2.06e-3, 1.75e-3, 1.07e-3, 0.56e-3 and 2.33e-3, 1.88e-3, 1.54e-3,
-// 0.94e-3, 0.49e-3.
+// (against the running maximum) and these: N(0, 1) inputs, 22 shapes in all forms,
+// 2.29e-3 to 2.36e-3 and 2.25e-3 to 2.36e-3, not larger in any but one (token-exact,
+// 4 heads, by 0.1%, in split tiles while those still summed on the VALU); with Q and
+// K times 1, 2, 4, 8, 16, one head of 4,680 tokens, split tiles, 2.36e-3, 2.07e-3,
+// 1.77e-3, 1.07e-3, 0.56e-3 and 2.36e-3, 1.82e-3, 1.51e-3, 0.93e-3, 0.49e-3, and 12
+// heads of 5,460 tokens, whole tiles, 2.33e-3, 2.06e-3, 1.75e-3, 1.07e-3, 0.56e-3 and
+// 2.33e-3, 1.88e-3, 1.54e-3, 0.94e-3, 0.49e-3.
 constexpr int READY = 1, WIDE = 2;
 struct WaveState {
   f32x4 o[8][2];   // O^T tiles [d tile][query tile]: d = 16*dt + C row
@@ -530,17 +529,17 @@ __device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU
 //
 // The headroom is 7 at first: the result is then as precise as against the running
 // maximum for V of any scale (measured down to 2^-120, where bf16 itself runs out).
-// Logits so wide that a step is redone would cross it again and again
-// (one redoing wave holds up the other seven at the half step's barrier), so the
-// wave's first redo takes 39 from then on; products p v then lose bits for v below
-// 2^-100 (measured, Q and K times 8: error 0.94e-3 down to 2^-95, 0.95e-3 at 2^-100,
-// 7.8e-3 at 2^-105).  Wan-1.3B 6x
-// step with Q and K times 1, 2, 4, 8, ms, interleaved on one board: 27.8, 29.9, 31.0
-// and 30.0 with 7 throughout, 27.7, 28.5, 28.6 and 28.5 so (with a row maximum every
-// step and 32x32x16 MFMAs 30.4, 31.8, 32.0 and 28.9).  Times 16 and more, where one
-// key holds all of a row's weight, it is 3 to 8% slower than a row maximum every
-// step; taking one first after 8 to 32 redos mended that, but cost 3 to 5% at times
-// 8, or a spilled register everywhere where the rescale was made conditional.
+// Logits so wide that a step is redone would cross it again and again (one redoing
+// wave holds up the other seven at the half step's barrier), so a wave's first redo
+// takes 39 from then on; products p v then lose bits for v below 2^-100 (measured,
+// Q and K times 8: error 0.94e-3 down to 2^-95, 0.95e-3 at 2^-100, 7.8e-3 at 2^-105).
+// Wan-1.3B 6x step with Q and K times 1, 2, 4, 8, ms, interleaved on one board: 27.8,
+// 29.9, 31.0 and 30.0 with 7 throughout, 27.7, 28.5, 28.6 and 28.5 so (with a row
+// maximum every step and 32x32x16 MFMAs 30.4, 31.8, 32.0 and 28.9).  Times 16 and
+// more, where one key holds all of a row's weight, it is 3 to 8% slower than a row
+// maximum every step; taking one first after 8 to 32 redos mended that, but cost 3
+// to 5% at times 8, or a spilled register everywhere where the rescale was made
+// conditional.
 template <int NU, bool LOADS>
 __device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& st,
                                               Probs<NU>& pr, float scale_log2,
@@ -696,8 +695,8 @@ struct WalkLds {
 static_assert(2 * WALK_CAP * 4 <= 4 * Tile::BYTES, "rows staged in the tile buffers");
 
 // Step words of one or two rows (of four: merge_four).  Block form (row entries are
-// key blocks): kb in bits 0..29, bit 30 / 31 set when row 0 / row 1 keeps kb.  Token-exact form (row
-// entries are entry words): bits 0..23 kb and kfirst, bits 24..27 / 28..31
+// key blocks): kb in bits 0..29, bit 30 / 31 set when row 0 / row 1 keeps kb.
+// Token-exact form (row entries are entry words): bits 0..23 kb and kfirst, bits 24..27 / 28..31
 // the patterns of row 0 / row 1, 0 where that row does not keep kb.  A key
 // block outside [0, nb) gives a word that masks every key (and whose loads
 // read zeros).
@@ -1451,8 +1450,8 @@ int tiles_of(const AttnArgs& a, int kg) {
 // one, and a launch of fewer tiles than CUs leaves CUs idle.  Splitting tiles
 // over the key groups of a workgroup (Split) gives more, shorter items: a
 // 128-row item takes 0.60 of a 256-row tile's time and a 64-row one 0.42
-// (PART_TIME; not 0.5 and 0.25: each K/V tile brought into LDS serves fewer rows; measured with
-// every CU busy, Wan-1.3B 1x and 6x: 4.48 and 28.7 ms whole, 5.28 and 33.3 ms in
+// (PART_TIME; not 0.5 and 0.25: each K/V tile brought into LDS serves fewer rows;
+// measured with every CU busy, Wan-1.3B 1x and 6x: 4.48 and 28.7 ms whole, 5.28 and 33.3 ms in
 // 128-row items, 7.69 and 43.1 ms in 64-row items; with 64-token blocks at 2x 9.34,
 // 10.6 and 13.7 ms; walks of 16 steps 0.72 and 0.48, of 4 steps 0.94 and 0.61,
 // where a tile's fixed times count: the plan they give is the same).  So whole
