@@ -104,9 +104,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int D = 128;             // head_dim
 // Distance (log2) of a row's reference above the largest score it was set from,
-// before and after the wave's first redo of a step (softmax_phase).
+// before and after the wave's first redo of a step, and the redos after which a
+// wave takes the row maximum ahead of every step (softmax_phase).
 constexpr float HEADROOM = 7.f;
 constexpr float WIDE_HEADROOM = 39.f;
+constexpr int MAX_REDOS = 12;
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
@@ -366,12 +368,13 @@ __device__ __forceinline__ void compute_scores(const char* lds_k, const bf16x8 (
 // 1.77e-3, 1.07e-3, 0.56e-3 and 2.36e-3, 1.82e-3, 1.51e-3, 0.93e-3, 0.49e-3, and 12
 // heads of 5,460 tokens, whole tiles, 2.33e-3, 2.06e-3, 1.75e-3, 1.07e-3, 0.56e-3 and
 // 2.33e-3, 1.88e-3, 1.54e-3, 0.94e-3, 0.49e-3.
-constexpr int READY = 1, WIDE = 2;
+constexpr int READY = 1, WIDE = 2, REDO = 4;
 struct WaveState {
   f32x4 o[8][2];   // O^T tiles [d tile][query tile]: d = 16*dt + C row
   float m[2];      // reference of the exponentials (log2 domain), the same in a row's four lanes
   f32x4 l[2];      // row sums
-  int flags;       // READY: every row has a finite m; WIDE: a step was redone
+  int flags;       // READY: every row has a finite m; WIDE: a step was redone; EAGER: REDO
+                   // times the steps redone
 };
 
 // Keys at or past N (ragged last block) do not exist: their scores become
@@ -445,8 +448,9 @@ struct Probs {
 
 // Raises the reference m of every row whose largest score of the step lies
 // above it, to `head` above that score, the others by `lift`, and rescales the rows'
-// O and l.
-template <int NU>
+// O and l.  FIRST: ahead of the step's probabilities, not because some are too large.
+// EAGER: see softmax_phase.
+template <int NU, bool FIRST, bool EAGER>
 __device__ __forceinline__ void raise_max(const Scores<NU>& sc, WaveState& st,
                                           float scale_log2, float head, float lift) {
   float mx[2];
@@ -459,19 +463,23 @@ __device__ __forceinline__ void raise_max(const Scores<NU>& sc, WaveState& st,
       for (int r = 0; r < 4; ++r) mx[qt] = fmaxf(mx[qt], sc.s[kt][qt][r]);
   }
   row_max(mx[0], mx[1]);
+  if (!(FIRST && EAGER) ||
+      __builtin_amdgcn_ballot_w64(mx[0] * scale_log2 > st.m[0] || mx[1] * scale_log2 > st.m[1])) {
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt) {
-    const float top = mx[qt] * scale_log2;
-    const float m = top > st.m[qt] ? top + head : st.m[qt] + lift;
-    const float a = m == st.m[qt] ? 1.f : __builtin_amdgcn_exp2f(st.m[qt] - m);
-    st.m[qt] = m;
-    st.l[qt][0] *= a;
+    for (int qt = 0; qt < 2; ++qt) {
+      const float top = mx[qt] * scale_log2;
+      const float m = top > st.m[qt] ? top + head : st.m[qt] + lift;
+      const float a = m == st.m[qt] ? 1.f : __builtin_amdgcn_exp2f(st.m[qt] - m);
+      st.m[qt] = m;
+      st.l[qt][0] *= a;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) st.o[dt][qt] *= a;
+      for (int dt = 0; dt < 8; ++dt) st.o[dt][qt] *= a;
+    }
   }
   const bool ready = __builtin_amdgcn_ballot_w64(st.m[0] == -__builtin_inff() ||
                                                  st.m[1] == -__builtin_inff()) == 0;
-  st.flags = (st.flags & WIDE) | (ready ? READY : 0);
+  st.flags = (st.flags & ~READY) |
+             (ready && (!EAGER || st.flags < MAX_REDOS * REDO) ? READY : 0);
 }
 
 // P = 2^(s*scale - m) in bf16 from one step's scores, with the tile loads in `sl`
@@ -536,25 +544,30 @@ __device__ __forceinline__ uint32_t probabilities(const Scores<NU>& sc, Probs<NU
 // Wan-1.3B 6x step with Q and K times 1, 2, 4, 8, ms, interleaved on one board: 27.8,
 // 29.9, 31.0 and 30.0 with 7 throughout, 27.7, 28.5, 28.6 and 28.5 so (with a row
 // maximum every step and 32x32x16 MFMAs 30.4, 31.8, 32.0 and 28.9).  Times 16 and
-// more, where one key holds all of a row's weight, it is 3 to 8% slower than a row
-// maximum every step; taking one first after 8 to 32 redos mended that, but cost 3
-// to 5% at times 8, or a spilled register everywhere where the rescale was made
-// conditional.
-template <int NU, bool LOADS>
+// more, where one key holds all of a row's weight, steps are redone even so: with
+// EAGER a wave that has redone MAX_REDOS steps raises m ahead of every step from then
+// on (READY stays off).  Wan-1.3B 1x, Q and K times 4, 8, 16, 32, ms, on one board:
+// 4.55, 4.57, 4.73, 4.83 without, 4.59, 4.49, 4.47, 4.45 with (row maximum every step
+// and 32x32x16 MFMAs: 5.13, 4.57, 4.48, 4.42).  Whole tiles of two query blocks only:
+// split tiles and tiles of four are well ahead of the latter at any width and would
+// pay 1% and up to 3% on ordinary inputs.
+template <int NU, bool EAGER, bool LOADS>
 __device__ __forceinline__ void softmax_phase(const Scores<NU>& sc, WaveState& st,
                                               Probs<NU>& pr, float scale_log2,
                                               const StepLoads& sl) {
   const int flags = __builtin_amdgcn_readfirstlane(st.flags);
   const bool first = !(flags & READY);
-  if (first) raise_max<NU>(sc, st, scale_log2, (flags & WIDE) ? WIDE_HEADROOM : HEADROOM, 0.f);
+  if (first)
+    raise_max<NU, true, EAGER>(sc, st, scale_log2, (flags & WIDE) ? WIDE_HEADROOM : HEADROOM,
+                               0.f);
   float m[2];
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt) m[qt] = st.m[qt] == -__builtin_inff() ? 0.f : st.m[qt];
   const uint32_t bits = probabilities<NU, LOADS>(sc, pr, m, scale_log2, sl);
   if (__builtin_amdgcn_ballot_w64((bits & 0x40004000u) != 0u) && !first) {
-    st.flags |= WIDE;
-    raise_max<NU>(sc, st, scale_log2, WIDE_HEADROOM,
-                  (flags & WIDE) ? 0.f : WIDE_HEADROOM - HEADROOM);
+    st.flags = EAGER ? (st.flags | WIDE) + REDO : st.flags | WIDE;
+    raise_max<NU, false, EAGER>(sc, st, scale_log2, WIDE_HEADROOM,
+                                (flags & WIDE) ? 0.f : WIDE_HEADROOM - HEADROOM);
     probabilities<NU, false>(sc, pr, st.m, scale_log2, sl);
   }
 }
@@ -984,6 +997,7 @@ __device__ __forceinline__ bool attn_tile(
   // Key blocks of a step that a wave's query block may not keep (gemm_phase): of a
   // tile in one query block none, of a wave whose keys lie in one key block one.
   constexpr int SKIP = !SPARSE ? 0 : QUAD ? 2 : PAIR ? 1 : 0;
+  constexpr bool EAGER = KG == 1 && !QUAD;       // softmax_phase
   // Four query blocks only in the block form: four 4-bit patterns and a key
   // block do not fit the token-exact form's words.
   static_assert(QUAD ? MODE == ATTN_BLOCK && SUBS == 2 : SP::ROWS <= 2 * BLOCK, "tile rows");
@@ -1190,7 +1204,7 @@ __device__ __forceinline__ bool attn_tile(
     compute_scores<NU>(k_lds, qf, sc, fa);   // S(0)
     int keep = mask_step(sc, w0, o0, upper);
     Probs<NU> pr;
-    if (lead) softmax_phase<NU, false>(sc, ws, pr, scale_log2, StepLoads{});   // P(0)
+    if (lead) softmax_phase<NU, EAGER, false>(sc, ws, pr, scale_log2, StepLoads{});   // P(0)
     __syncthreads();
     for (int j = 0; j < n; ++j) {
       // Word of step j+3 from the walk's LDS, read now and used at the end of
@@ -1213,14 +1227,14 @@ __device__ __forceinline__ bool attn_tile(
         keep = mask_step(sc, w1, o1, false);
       } else {
         if constexpr (KG == 1) issue_step_loads(sl);
-        softmax_phase<NU, (KG > 1)>(sc, ws, pr, scale_log2, sl);
+        softmax_phase<NU, EAGER, (KG > 1)>(sc, ws, pr, scale_log2, sl);
       }
       __syncthreads();
       // half-period 2j+1
       if (lead) {
         if (j + 1 < n) {
           if constexpr (KG == 1) issue_step_loads(sl);
-          softmax_phase<NU, false>(sc, ws, pr, scale_log2, sl);
+          softmax_phase<NU, EAGER, false>(sc, ws, pr, scale_log2, sl);
         }
       } else {
         gemm_phase<NU, SKIP, false>(kj1, vj, qf, sc, pr, ws, fa, ones, keep, sl);

@@ -220,24 +220,26 @@ def test_reference_is_raised_within_a_walk(peak):
     _check(out, ref, list(range(H)), N, 128)
 
 
-@pytest.mark.parametrize("v_exp", [0, -90])
+@pytest.mark.parametrize("H,P,ramp,v_exp", [(64, 333, 30.0, 0), (64, 333, 30.0, -90),
+                                            (16, 1363, 350.0, 0), (1, 1363, 350.0, 0)])
 @pytest.mark.parametrize("form,block", [("dense", 128), ("block", 128), ("block", 64),
                                         ("exact", 128), ("exact", 64)])
-def test_reference_is_raised_in_whole_tiles(form, block, v_exp):
+def test_reference_is_raised_in_whole_tiles(form, block, H, P, ramp, v_exp):
     """The same in launches of whole tiles (256 of 256 rows; token-exact with
     64-token blocks 512 of 128): rows whose reference rises by more than either
     headroom, step after step, beside rows that never raise it; V down to
     2^-90, whose products with the smallest references still are normal
-    numbers."""
-    H, P, T = 64, 333, 3
+    numbers; and walks of 32 steps that would redo nearly all of them (a wave
+    takes the row maximum first after 12), also in 64-row parts (one head)."""
+    T = 3
     N = P * T + 1
-    _say(f"[split] raised reference, whole tiles, {form} B={block} V*2^{v_exp}")
+    _say(f"[split] raised reference, {form} B={block} H={H} N={N} V*2^{v_exp}")
     q, k, v = make_qkv(H, N, seed=4)
     q[:, 1::3] *= 0.02
-    k *= torch.linspace(30.0, 0.1, N).view(1, N, 1).to(torch.bfloat16)
+    k *= torch.linspace(ramp, 0.1, N).view(1, N, 1).to(torch.bfloat16)
     k[:, 7] = (q[:, 702] * 3).to(torch.bfloat16)
     vd = (v.float() * 2.0 ** v_exp).to(torch.bfloat16).cuda()
-    heads, nb = [0, H - 1], -(-N // block)
+    heads, nb = sorted({0, H - 1}), -(-N // block)
     qs, ks, vs = (x[heads].float().numpy() for x in (q, k, v))
     if form == "exact":
         p = L.Params(window=0, tper=3, text_tokens=1)
@@ -252,7 +254,8 @@ def test_reference_is_raised_in_whole_tiles(form, block, v_exp):
         s = np.where(att[seg][:, seg], qs @ ks.transpose(0, 2, 1) / np.sqrt(128.0), -np.inf)
         pr = np.exp(s - s.max(-1, keepdims=True))
         full = (pr / pr.sum(-1, keepdims=True)) @ vs
-        ref = {(h, qb): full[h, qb * block:(qb + 1) * block] for h in range(2) for qb in range(nb)}
+        ref = {(h, qb): full[h, qb * block:(qb + 1) * block]
+               for h in range(len(heads)) for qb in range(nb)}
     else:
         if form == "block":
             rp, ci = _random_csr(nb, block, set())
