@@ -81,9 +81,9 @@
 //   the softmax phase (112 VALU instructions and 64 exponentials a step beside
 //   136 MFMAs, and 8 tile loads of about 67 cycles) takes 2,700 cycles, and the
 //   GEMM phase (136 MFMAs of 16 cycles, 96 LDS reads of about 2.3) 2,600.
-//   Wan-1.3B 6x, 12 heads, step 10: 31.9 ms with 32x32x16 MFMAs and a row
-//   maximum per step, 28.9 ms now (1.38 PFLOP/s; a large bf16 matrix product
-//   reaches 1.54), all on one board, one of the slower ones.
+//   Wan-1.3B 6x, 12 heads, step 10: 31.4 ms with 32x32x16 MFMAs and a row
+//   maximum per step, 28.3 ms now (1.42 PFLOP/s; a large bf16 matrix product
+//   reaches 1.59), all on one board.
 //
 // Online softmax (fp32, base 2): p = exp2(s*log2(e)/sqrt(d) - m), l = sum p,
 // with a reference m per row that is raised, and O and l rescaled, only when
